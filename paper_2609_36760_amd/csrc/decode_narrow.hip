@@ -1,37 +1,54 @@
-// Decode attention for few query rows per sequence (16 per workgroup), the
-// regime of 16 heads and one query token (Appendix F.1, "Native Attention"),
-// where the 128-row kernel of decode_attn.hip would leave 7/8 of every matrix
-// instruction idle.  Same computation and results contract: absorbed MLA
-// scores z_t = tau (q_lat . C_hat_t + q_rope . K_hat_t), softmax, latent
-// aggregation O = A C_hat (Sec. 2.1, eq. mla_compact), split partials as in
-// Appendix C.5 "Global attention normalization", BF16 protection of sink and
+// Decode attention for few query rows per sequence (up to 32 per wave), the
+// regime of 16 heads and one query token (Appendix F.1, "Native Attention") or
+// of 32 rows, where the 128-row kernel of decode_attn.hip would leave most of
+// every matrix instruction idle.  Same computation and results contract:
+// absorbed MLA scores z_t = tau (q_lat . C_hat_t + q_rope . K_hat_t), softmax,
+// latent aggregation O = A C_hat (Sec. 2.1, eq. mla_compact), split partials as
+// in Appendix C.5 "Global attention normalization", BF16 protection of sink and
 // recent tokens as in Appendix C.5 "BF16 protection and cache lifecycle".
 //
-// Workgroup = one wave (64 lanes), several per CU; no workgroup barriers.
-// It owns one (sequence or key split, block of 16 query rows).  Lane l works
-// on query row l % 16 and lane group g = l / 16.
+// A wave owns kR = 16 or 32 query rows and a key range: a work item (sequence
+// or key split), or one of the kW contiguous parts of it that the kW waves of a
+// workgroup share and merge at the end.  Waves run one per SIMD, without
+// barriers in the loop.  Lane l works in lane group g = l / 16 on index
+// i = l % 16.
 //
-// Per 16-token tile (low-bit cache):
-//   1. the packed bytes are copied HBM -> LDS by direct-to-LDS loads two tiles
-//      ahead, gathered chunk-major (16-byte chunk j of token m at chunk slot
-//      16 j + m) so that the per-lane code reads below are bank-conflict-free;
-//   2. scores S^T[token][row] = K_tile . Q^T with v_mfma_f32_16x16x32_f16: the
-//      A operand of k-step kk is token l % 16, channels 32 kk + 8 g .. +8 --
-//      one 32-bit word of 4-bit codes, dequantized in registers (x_hat =
-//      scale * (q - zero), one fp16 rounding); the dequantized content
-//      channels are also stored to an fp16 tile in LDS;
-//   3. softmax: a lane holds tokens 4 g .. 4 g + 3 of its row; maxima and sums
-//      combine the four lane groups with v_permlane16/32_swap;
-//   4. aggregation O^T[channel][row] += V^T . P^T with v_mfma_f32_16x16x16_f16
-//      (32 channel blocks, K = the 16 tokens): V^T read transposed from the
-//      fp16 tile with ds_read_b64_tr_b16, P^T straight from the score
-//      registers (the lane's four tokens are the B operand's K slice).
-// BF16 rows (the BF16 cache, and protected rows from a protection buffer)
-// are staged raw into a padded tile and feed both products directly.
+// Per tile of kTok tokens (32 at 16 rows, 16 at 32 rows; low-bit cache):
+//   1. each lane loads its own codes from the page straight into registers: of
+//      token i (of each 16-token block) the 32 channels 128 j + 32 g .. of each
+//      128-channel slice j, one 16-byte load (4 bits) -- 64 consecutive bytes
+//      per token and load.  A slice's registers are loaded for the next tile as
+//      soon as this tile has used them, one step ahead of their use;
+//   2. scores S^T[token][row] = K_tile . Q^T with v_mfma_f32_16x16x32_f16.  The
+//      order of the channels in a product's K does not matter as long as both
+//      operands agree: k-step 4 j + w takes channels 128 j + 32 g + 8 w .. +8
+//      from lane group g, one 32-bit word of 4-bit codes, dequantized in
+//      registers (x_hat = scale * (q - zero), one fp16 rounding); the queries
+//      are loaded in the same order.  The dequantized content channels are also
+//      stored to an fp16 tile in LDS;
+//   3. softmax: 16 rows: a lane holds tokens 4 g .. 4 g + 3 of each block for
+//      row i; 32 rows: v_permlane16_swap gives lane l tokens 8 (l / 32) .. +8 of
+//      row l % 32;
+//   4. aggregation O^T[channel][row] += V^T . P^T over the tile's tokens with
+//      v_mfma_f32_16x16x32_f16 (16 rows) or v_mfma_f32_32x32x16_f16 (32 rows):
+//      V^T read transposed from the fp16 tile with ds_read_b64_tr_b16, P^T
+//      straight from the score registers.
+// BF16 rows (the BF16 cache, and protected rows from a protection buffer) are
+// staged raw into a padded tile of 16 tokens and feed both products directly.
 //
 // Online softmax as in decode_attn.hip: a per-row reference (log2 units) that
 // moves only when a tile exceeds it by more than 2^10, the accumulators
 // rescaled on the move; the true maximum is tracked for the split partials.
+//
+// What bounds it.  A wave alone on its SIMD issues an 8-byte vector instruction
+// every 5.1 cycles and a 4-byte one every 4.2 (measured, dependent or not), and
+// products hide behind them, so the time is the instruction count: 849 per 32
+// tokens at 16 rows, 579 of them vector instructions and 468 of those the
+// dequantization; 547 per 16 tokens at 32 rows.  Staging the codes through LDS
+// (20 more LDS reads and 6 direct-to-LDS loads per 16 tokens), a 16-token step
+// and K = 16 aggregation products took about 480 instructions per 16 tokens.
+// Long contexts are also held by the board's power limit: 32 x 64K at 16 heads
+// takes 180 us (204 us so) at 1 389 W and 2.06 GHz (2.35 GHz so).
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -48,54 +65,54 @@ using namespace kc;
 
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kRows = 16;           // query rows per workgroup
-static_assert(kRows == kNarrowRowsPerBlock, "launch shape the host checks");
-constexpr int kTok = 16;            // tokens per tile
-constexpr int kQSteps = 18;         // 576 channels / 32 per k-step
+constexpr int kMaxRows = kNarrowRows;   // rows of the widest wave
 constexpr int kDc = 512;
+constexpr int kQSteps = 18;         // 576 channels / 32 per k-step
 constexpr float kRefSlack = 10.0f;
+constexpr int kCus = 256;           // compute units; one wave per SIMD, four per unit
 constexpr float kLn2 = 0.693147180559945309f;
 
 // LDS tiles, in 16-byte units.  Row r of the fp16 content tile starts at unit
 // 66 r + r / 8, row r of a raw bf16 tile at 74 r + r / 8: the dequantization
 // stores and score reads (16 rows, one chunk each) and the transposing reads
-// (8 rows, two chunks each, per half wave) then fall on distinct banks.
+// (per half wave 8 rows of 32 bytes, or 4 rows of two 32-byte pieces 128 bytes
+// apart) then fall on distinct banks.
 __host__ __device__ constexpr int f16_row(int r) { return 66 * r + (r >> 3); }
 __host__ __device__ constexpr int bf_row(int r) { return 74 * r + (r >> 3); }
-constexpr int kF16TileBytes = 16 * (f16_row(15) + 64);
-constexpr int kBfUnits = (bf_row(15) + 72 + 63) / 64 * 64;
+constexpr int f16_tile_bytes(int tokens) { return 16 * (f16_row(tokens - 1) + 64); }
+constexpr int kBfTok = 16;          // tokens per bf16 tile
+constexpr int kBfUnits = (bf_row(kBfTok - 1) + 72 + 63) / 64 * 64;
 constexpr int kBfTileBytes = 16 * kBfUnits;
 constexpr int kBfLoads = kBfUnits / 64;
+constexpr int kBfSlots = 2;         // tile slots; the next tile is staged one tile ahead
 static_assert(kBfLoads == 19, "bf16 tile staging loads");
 
-// Narrow configuration per cache kind.  Low-bit staging slot (units): content
-// codes chunk-major [cc/16 chunks][16 tokens], RoPE codes [2][16], metadata
-// [2][16] (fp16 content pairs, or the paper's 32-byte record), and for fp16
-// metadata the RoPE pairs token-major (4 units).
 template <int KIND> struct NCfg {
-    static constexpr bool lowbit = true;
+    static constexpr bool lowbit = KIND != KIND_BF16;
     static constexpr bool pmeta = KIND == KIND_C4R4P || KIND == KIND_C2R4P;
     static constexpr int cbits = (KIND == KIND_C4R4 || KIND == KIND_C4R4P) ? 4 : 2;
     static constexpr int cc = 512 * cbits / 8;            // content code bytes per token
-    static constexpr int u_rc = cc, u_mc = cc + 32, u_mr = cc + 64;
-    static constexpr int units = u_mr + (pmeta ? 0 : 4);
-    static constexpr int loads = (units + 63) / 64;
-    static constexpr int stage_bytes = 16 * units;
-    static constexpr int NS = 3, D = 2;                   // staging slots, tiles ahead
-    static constexpr int lds = NS * stage_bytes + kF16TileBytes;
-};
-template <> struct NCfg<KIND_BF16> {
-    static constexpr bool lowbit = false;
-    static constexpr int loads = kBfLoads;
-    static constexpr int NS = 2, D = 1;                   // tile slots, tiles ahead
-    static constexpr int lds = NS * kBfTileBytes;
 };
 
-template <int KIND>
-constexpr int narrow_lds(bool prot) {
-    return prot && NCfg<KIND_BF16>::lds > NCfg<KIND>::lds ? NCfg<KIND_BF16>::lds : NCfg<KIND>::lds;
+// Tokens per low-bit tile.  16 rows: 32, so that the softmax's and the step's
+// fixed work is shared by two 16-token blocks and the aggregation runs at
+// K = 32.  32 rows: 16 (the output accumulators and the queries take 400 of the
+// 512 registers, which leaves room for one block's codes).
+constexpr int narrow_tok(int rows) { return rows == 16 ? 32 : 16; }
+
+// LDS of one wave: the fp16 tile or the bf16 slots, reused by the epilogue (the
+// rows on their way out; with several waves the fp32 rows they merge, in two
+// halves of the channels at 32 rows).
+constexpr int kOutPitch = 1040;
+constexpr int merge_pitch(int rows) { return (rows == 16 ? 2048 : 1024) + 16; }
+template <int KIND, bool kProt, int kR, int kW>
+constexpr int narrow_lds() {
+    int n = NCfg<KIND>::lowbit ? f16_tile_bytes(narrow_tok(kR)) : 0;
+    if (kProt || !NCfg<KIND>::lowbit) n = n > kBfSlots * kBfTileBytes ? n : kBfSlots * kBfTileBytes;
+    const int out = kW == 1 ? kR * kOutPitch : kR * merge_pitch(kR);
+    n = n > out ? n : out;
+    return (n + 1023) / 1024 * 1024;
 }
 
 template <int N>
@@ -118,28 +135,50 @@ __device__ __forceinline__ float sum4(float v) {
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// Staging of one low-bit tile: load k (of NCfg::loads) covers slot units
-// 64 k .. 64 k + 63 (lane = unit - 64 k).  Tokens at or past nvalid re-read
-// token nvalid - 1 (the RoPE pairs: four tokens per chunk, read as they are).
-// The content codes fill whole loads (cc / 64 of them); the next load carries
-// the RoPE codes (lanes 0-31) and the metadata (lanes 32-63); with fp16
-// metadata a last load brings the RoPE pairs (lanes 0-3).
-template <int KIND>
-__device__ __forceinline__ void stage_narrow_lowbit(int k, const uint8_t* page, int po, int nvalid,
-                                                    const PageGeom& g, uint32_t lds, int lane) {
-    using C = NCfg<KIND>;
-    static_assert(C::u_rc % 64 == 0 && C::u_mr == C::u_rc + 64, "region boundaries on load boundaries");
-    const int last = nvalid - 1;
-    if (k < C::u_rc / 64) {
-        const int u = 64 * k + lane;
-        dma16_m0(page, (po + min(u & 15, last)) * C::cc + 16 * (u >> 4), lds + 64 * 16 * k);
-    } else if (k == C::u_rc / 64) {
-        const int v = lane & 31;
-        const int base = lane < 32 ? g.off_cr : g.off_mc;
-        dma16_m0(page, base + (po + min(v & 15, last)) * 32 + 16 * (v >> 4), lds + 64 * 16 * k);
-    } else if (lane < 4) {
-        dma16_m0(page, g.off_mr + po * 4 + 16 * lane, lds + 64 * 16 * k);
-    }
+// max / sum over lane ^ 32
+__device__ __forceinline__ float max2(float v) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float sum2(float v) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// Score product of a 32-row wave, accumulating in vector registers: the output
+// accumulators fill the accumulation registers, and a score tile kept there
+// would push output tiles out and back on every step.  Issued as inline
+// assembly, so the waits the compiler would insert are written here: two wait
+// states between the vector instruction that wrote an operand and the product,
+// and score_ready() before vector instructions read the results (12, more than
+// a 16 x 16 x 32 product's result needs).
+__device__ __forceinline__ void score_mfma(f32x4& c, f16x8 a, f16x8 b, bool first) {
+    if (first)
+        asm volatile("s_nop 1\n\tv_mfma_f32_16x16x32_f16 %0, %1, %2, 0" : "=&v"(c) : "v"(a), "v"(b));
+    else
+        asm volatile("s_nop 1\n\tv_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
+}
+__device__ __forceinline__ void score_mfma(f32x4& c, bf16x8 a, bf16x8 b, bool first) {
+    if (first)
+        asm volatile("s_nop 1\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=&v"(c) : "v"(a), "v"(b));
+    else
+        asm volatile("s_nop 1\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
+}
+__device__ __forceinline__ void score_ready(f32x4& c0, f32x4& c1) {
+    asm volatile("s_nop 7\n\ts_nop 3" : "+v"(c0), "+v"(c1));
+}
+
+// 4 x 4 transpose of registers across lane groups: lane group g of register w
+// receives what lane group w of register g held.
+__device__ __forceinline__ void group_transpose(uint32_t& a0, uint32_t& a1, uint32_t& a2, uint32_t& a3) {
+    const auto p = __builtin_amdgcn_permlane32_swap(a0, a2, false, false);
+    const auto q = __builtin_amdgcn_permlane32_swap(a1, a3, false, false);
+    const auto u = __builtin_amdgcn_permlane16_swap(p[0], q[0], false, false);
+    const auto v = __builtin_amdgcn_permlane16_swap(p[1], q[1], false, false);
+    a0 = u[0];
+    a1 = u[1];
+    a2 = v[0];
+    a3 = v[1];
 }
 
 // Staging of one raw bf16 tile (576 channels per row) into the padded layout:
@@ -155,7 +194,7 @@ __device__ __forceinline__ void stage_narrow_bf16(int k, const uint8_t* src, Row
     dma16_m0(src, row_start(min(r, nvalid - 1)) + 16 * col, lds + 64 * 16 * k);
 }
 
-// Dequantize 8 channels into fp16 pairs (2p, 2p+1).  In the code layout a
+// Dequantization of 8 channels into fp16 pairs (2p, 2p+1).  In the code layout a
 // channel pair sits at one bit offset of the two 16-bit halves of a word: the
 // 8 channels are the word's pairs at bit offsets sh0 + CBITS p (a 4-bit word
 // holds exactly 8 channels, sh0 = 0; a 2-bit word 16, sh0 = 0 or 8).  A pair
@@ -165,30 +204,33 @@ __device__ __forceinline__ void stage_narrow_bf16(int k, const uint8_t* src, Row
 // adds zo = -(1024 / 2^o + zero) (zo[o / 2 - 1]).  Both are exact, so the
 // word is shifted only by whole bytes, and the one rounding is the multiply
 // by the scale.
-template <int CBITS>
-__device__ __forceinline__ f16x8 dequant8(uint32_t w, int sh0, f16x2 zz, const f16x2* zo, f16x2 ss) {
-    uint32_t o[4];
-    if constexpr (CBITS == 4) {
-        const uint32_t w8 = w >> 8;
+struct DqWord {
+    f16x2 x[4];
+    template <int CBITS>
+    __device__ __forceinline__ void extract(uint32_t w, int sh0) {
+        const uint32_t w0 = CBITS == 4 ? w : w >> sh0, w8 = w >> 8;
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
-            const uint32_t src = p < 2 ? w : w8;
-            const f16x2 x = __builtin_bit_cast(f16x2, and_or(src, (p & 1) ? 0x00F000F0u : 0x000F000Fu, 0x64006400u));
-            const f16x2 d = (p & 1) ? __builtin_elementwise_fma(x, f16x2{0.0625f16, 0.0625f16}, zo[1]) : x - zz;
-            o[p] = __builtin_bit_cast(uint32_t, d * ss);
-        }
-    } else {
-        const uint32_t ws = w >> sh0;
-#pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            const f16x2 x = __builtin_bit_cast(f16x2, and_or(ws, 0x00030003u << (2 * p), 0x64006400u));
-            constexpr _Float16 kInv[4] = {1.0f16, 0.25f16, 0.0625f16, 0.015625f16};
-            const f16x2 d = p == 0 ? x - zz : __builtin_elementwise_fma(x, f16x2{kInv[p], kInv[p]}, zo[p - 1]);
-            o[p] = __builtin_bit_cast(uint32_t, d * ss);
+            const uint32_t mask = CBITS == 4 ? ((p & 1) ? 0x00F000F0u : 0x000F000Fu) : 0x00030003u << (2 * p);
+            x[p] = __builtin_bit_cast(f16x2, and_or(CBITS == 4 && p >= 2 ? w8 : w0, mask, 0x64006400u));
         }
     }
-    return __builtin_bit_cast(f16x8, make_uint4(o[0], o[1], o[2], o[3]));
-}
+    template <int CBITS>
+    __device__ __forceinline__ void center(f16x2 zz, const f16x2* zo) {
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            constexpr _Float16 kInv[4] = {1.0f16, 0.25f16, 0.0625f16, 0.015625f16};
+            const int h = CBITS == 4 ? 2 * (p & 1) : p;         // half the pair's bit offset in its byte
+            x[p] = h == 0 ? x[p] - zz : __builtin_elementwise_fma(x[p], f16x2{kInv[h], kInv[h]}, zo[h - 1]);
+        }
+    }
+    __device__ __forceinline__ f16x8 scaled(f16x2 ss) const {
+        uint32_t o[4];
+#pragma unroll
+        for (int p = 0; p < 4; ++p) o[p] = __builtin_bit_cast(uint32_t, x[p] * ss);
+        return __builtin_bit_cast(f16x8, make_uint4(o[0], o[1], o[2], o[3]));
+    }
+};
 
 // zo[k] = -(1024 / 2^o + zero) for o = 2 (k + 1), from zz = 1024 + zero
 // (exact: integers and quarters below 1024).
@@ -249,16 +291,45 @@ __device__ __forceinline__ void narrow_append(const DecodeArgs& a, int b, int L,
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
-// ---------------------------------------------------------------------------
-template <int KIND, bool kProt>
-__global__ __launch_bounds__(64) void narrow_kernel(DecodeArgs a) {
-    __shared__ __attribute__((aligned(1024))) uint8_t smem[narrow_lds<KIND>(kProt)];
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-    const int lane = threadIdx.x;
-    const int g = lane >> 4;            // lane group: tokens 4g..4g+3 of a tile, k slice 8g..8g+7
-    const int li = lane & 15;           // query row within the block; token of the score A operand
+// A load of the packed cache: base + 32-bit lane offset, marked non-temporal
+// (the cache bytes are read once per step).
+template <class T>
+__device__ __forceinline__ T load_nt(const uint8_t* base, uint32_t off) {
+    return __builtin_nontemporal_load(reinterpret_cast<const T*>(base + off));
+}
+
+// table[index], waited for on the spot.  Inline assembly, so that the compiler
+// does not count it among the loads in flight: a load on one side of a branch
+// makes it wait for all of them at the loop's start.
+__device__ __forceinline__ int load_waited(const int32_t* table, int index) {
+    int v;
+    asm volatile("global_load_dword %0, %1, %2\n\ts_waitcnt vmcnt(0)"
+                 : "=&v"(v)
+                 : "v"(index * 4), "s"(table)
+                 : "memory");
+    return v;
+}
+
+// ---------------------------------------------------------------------------
+template <int KIND, bool kProt, int kR, int kW>
+__global__ __launch_bounds__(64 * kW) __attribute__((amdgpu_waves_per_eu(1, 1)))
+void narrow_kernel(DecodeArgs a) {
+    static_assert(kR == 16 || kR == kMaxRows, "rows per wave");
+    constexpr int kLds = narrow_lds<KIND, kProt, kR, kW>();
+    static_assert(kLds * kW <= 160 * 1024 && (kW > 1 || 4 * kLds <= 160 * 1024), "one wave per SIMD fits the LDS");
+    __shared__ __attribute__((aligned(1024))) uint8_t smem_all[kLds * kW];
+
+    const int lane = threadIdx.x & 63;
+    const int wave = kW == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    uint8_t* smem = smem_all + wave * kLds;
+    const int g = lane >> 4;            // lane group
+    const int li = lane & 15;           // index in the group: token of the score A operand, row of its B operand
+    const int half = lane >> 5;
     const int rows_total = a.s_q * a.H;
-    const int RB = (rows_total + kRows - 1) / kRows;
+    const int RB = (rows_total + kR - 1) / kR;
 
     // Block -> (work item, row block): contiguous work items per XCD (block
     // id mod 8), as in decode_attn.hip.
@@ -298,117 +369,129 @@ __global__ __launch_bounds__(64) void narrow_kernel(DecodeArgs a) {
     const int L = min(max(Lraw, 0), a.max_pages * P);
     const int32_t* bt = a.block_table + static_cast<int64_t>(b) * a.max_pages;
 
-    const int row = rb * kRows + li;
+    // this lane's query row in the softmax and the output (li, or l % 32)
+    const int lrow = kR == 16 ? li : (lane & 31);
+    const int row = rb * kR + lrow;
     const bool row_ok = row < rows_total;
     const int qi = row_ok ? row / a.H : 0;
-    const int h = row_ok ? row % a.H : 0;
-    const int64_t qrow = (static_cast<int64_t>(b) * a.s_q + qi) * a.H + h;
 
     float m_ref = -INFINITY, m_true = -INFINITY, l_run = 0.0f;
-    f32x4 acc[32];
+    // output accumulators.  16 rows: acc[m], channels 16 m + 4 g + v of row li;
+    // 32 rows: acc[m], channels out_channel(m, 8 (v / 4) + 4 half + v % 4) of row l % 32
+    constexpr int kAccs = kR == 16 ? 32 : 16;
+    using AccT = std::conditional_t<kR == 16, f32x4, f32x16>;
+    constexpr int kAccLen = kR == 16 ? 4 : 16;
+    AccT acc[kAccs];
 #pragma unroll
-    for (int m = 0; m < 32; ++m) acc[m] = f32x4{};
+    for (int m = 0; m < kAccs; ++m) acc[m] = AccT{};
 
     const uint8_t* ring_base = nullptr;
     int ring_rows = 1, ring_nsink = 0, ring_q0 = 0;
 
+    // Transposing reads of V^T from a tile with row starts `rowf` (in units):
+    // 16 rows: product m takes channels 16 m ..; lane group g's first read
+    // covers tokens 4 g .. of the tile (the second, K = 32, 16 tokens on).
+    // 32 rows: product m takes channels 16 x .. (lanes with l / 16 even) and
+    // 16 (x + 4) .. (odd), x = 8 (m / 4) + m % 4, tokens 8 half .. + 3, then + 4 .. + 7.
+    auto tr_lane_off = [&](auto rowf) {
+        return kR == 16 ? 16 * rowf(4 * g + (li >> 2)) + 8 * (li & 3)
+                        : 16 * rowf(8 * half + (li >> 2)) + 128 * (g & 1) + 8 * (li & 3);
+    };
+    auto tr_imm = [](int m) { return kR == 16 ? 32 * m : 32 * (8 * (m >> 2) + (m & 3)); };
+    auto tr_read = [](const uint8_t* p) { return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)p); };
+
     // One phase over keys [t_begin, t_end) in one representation (see
     // decode_attn.hip): PK is the cache kind whose pipeline runs; kRing reads
     // bf16 rows of the protection buffer.  This lane's row sees keys
-    // t_lo <= t < lim.
-    auto run = [&](auto kind_c, auto ring_c, const int t_begin, const int t_end, const int t_lo,
-                   const int lim) __attribute__((always_inline)) {
+    // t_lo <= t < lim; every valid row sees t < full_lim.
+    auto run = [&](auto kind_c, auto ring_c, const int t_begin, const int t_end, const int t_lo, const int lim,
+                   const int full_lim) __attribute__((always_inline)) {
         constexpr int PK = decltype(kind_c)::value;
         constexpr bool kRing = decltype(ring_c)::value;
         using C = NCfg<PK>;
         using OpT = std::conditional_t<C::lowbit, f16x8, bf16x8>;
+        constexpr int kTok = C::lowbit ? narrow_tok(kR) : kBfTok;
+        constexpr int kNB = kTok / 16;          // 16-token blocks per tile
+        constexpr int kNR = kR / 16;            // 16-row blocks
+        constexpr int kScores = 4 * kNB * kNR;  // scores per lane and tile
         const int n_tiles = t_end > t_begin ? (t_end - t_begin + kTok - 1) / kTok : 0;
         (void)t_lo;
+        if (n_tiles == 0) return;
 
-        // queries (B operand of the scores): k-step kk holds channels 32 kk + 8 g .. +8 of row li
-        OpT qf[kQSteps];
-        {
-            const uint16_t* ql = a.q_lat + qrow * kDc + 8 * g;
-            const uint16_t* qr = a.q_rope + qrow * 64 + 8 * g;
+        // queries: B operand of the scores.  BF16 rows: k-step kk of row block r
+        // holds channels 32 kk + 8 g .. +8 of row 16 r + li.  Low-bit tiles take the
+        // order of the code loads: k-step 4 j + w holds channels 128 j + 32 g + 8 w
+        // .. +8.  Read in that order each load would touch 64 separate pieces; they
+        // are read in the plain order (64 bytes of a row per load) and the four
+        // loads of a slice transposed across the lane groups.
+        OpT qf[kNR][kQSteps];
+        uint4 rawq[kNR][kQSteps];
+        auto read_q = [&]() __attribute__((always_inline)) {
 #pragma unroll
-            for (int kk = 0; kk < kQSteps; ++kk) {
-                // rows past the end read a valid row; their results are never stored
-                const uint4 v = *reinterpret_cast<const uint4*>(kk < 16 ? ql + 32 * kk : qr + 32 * (kk - 16));
-                if constexpr (C::lowbit)
-                    qf[kk] = __builtin_bit_cast(f16x8, make_uint4(bf16x2_to_f16x2(v.x), bf16x2_to_f16x2(v.y),
-                                                                  bf16x2_to_f16x2(v.z), bf16x2_to_f16x2(v.w)));
-                else
-                    qf[kk] = __builtin_bit_cast(bf16x8, v);
-                // kept in accumulation registers, which the score products read
-                // directly as their B operand
-                asm volatile("" : "+a"(qf[kk]));
+            for (int r = 0; r < kNR; ++r) {
+                // rows past the end read row 0 of the sequence; their results are never stored
+                const int rr = rb * kR + 16 * r + li;
+                const int64_t qrow = static_cast<int64_t>(b) * rows_total + (rr < rows_total ? rr : 0);
+                const uint16_t* ql = a.q_lat + qrow * kDc + 8 * g;
+                const uint16_t* qr = a.q_rope + qrow * 64 + (C::lowbit ? 16 : 8) * g;
+#pragma unroll
+                for (int kk = 0; kk < kQSteps; ++kk)
+                    rawq[r][kk] = *reinterpret_cast<const uint4*>(kk < 16 ? ql + 32 * kk : qr + (C::lowbit ? 8 : 32) * (kk - 16));
             }
-        }
-
-        auto slot_base = [&](int j) {
-            if constexpr (C::lowbit) return smem + slot_offset(j, C::NS, C::stage_bytes);
-            else return smem + slot_offset(j, C::NS, kBfTileBytes);
         };
-        int st_pg = t_begin / P, st_po = t_begin % P, pid_pg = -1, pid = 0;   // next tile to stage
-        auto issue_tile = [&](int j) __attribute__((always_inline)) {
-            const int t0 = t_begin + min(j, n_tiles - 1) * kTok;   // past the end: the last tile again
-            const int nvalid = min(t_end - t0, kTok);
-            const uint32_t lds = lds_addr(slot_base(j));
-            if constexpr (kRing) {
-                auto row_start = [&](int tok) {
-                    const int v = t0 + tok;
-                    const int x = ring_q0 + (v - ring_nsink);       // < 2 * recent
-                    const int r = v < ring_nsink ? v : a.sink + (x >= a.recent ? x - a.recent : x);
-                    return min(r, ring_rows - 1) * 1152;
-                };
+        auto set_q = [&]() __attribute__((always_inline)) {
 #pragma unroll
-                for (int k = 0; k < C::loads; ++k) stage_narrow_bf16(k, ring_base, row_start, nvalid, lds, lane);
-            } else {
-                // tiles are issued in order; a 16-token tile never crosses a page
-                // (t_begin and the page size are multiples of 32), and the page
-                // id is fetched once per page
-                if (st_pg != pid_pg) {
-                    pid = load_page_id(bt, st_pg);
-                    pid = min(max(pid, 0), static_cast<int>(a.num_pages - 1));
-                    pid_pg = st_pg;
-                }
-                const uint8_t* page = a.cache + static_cast<int64_t>(pid) * a.g.page_bytes;
-                const int po = st_po;
-                if (j < n_tiles - 1) {
-                    st_po += kTok;
-                    if (st_po == P) {
-                        st_po = 0;
-                        ++st_pg;
-                    }
-                }
+            for (int r = 0; r < kNR; ++r) {
                 if constexpr (C::lowbit) {
 #pragma unroll
-                    for (int k = 0; k < C::loads; ++k) stage_narrow_lowbit<PK>(k, page, po, nvalid, a.g, lds, lane);
-                } else {
-                    auto row_start = [&](int tok) { return (po + tok) * 1152; };
+                    for (int j = 0; j < 4; ++j) {
+                        group_transpose(rawq[r][4 * j].x, rawq[r][4 * j + 1].x, rawq[r][4 * j + 2].x, rawq[r][4 * j + 3].x);
+                        group_transpose(rawq[r][4 * j].y, rawq[r][4 * j + 1].y, rawq[r][4 * j + 2].y, rawq[r][4 * j + 3].y);
+                        group_transpose(rawq[r][4 * j].z, rawq[r][4 * j + 1].z, rawq[r][4 * j + 2].z, rawq[r][4 * j + 3].z);
+                        group_transpose(rawq[r][4 * j].w, rawq[r][4 * j + 1].w, rawq[r][4 * j + 2].w, rawq[r][4 * j + 3].w);
+                    }
+                }
 #pragma unroll
-                    for (int k = 0; k < C::loads; ++k) stage_narrow_bf16(k, page, row_start, nvalid, lds, lane);
+                for (int kk = 0; kk < kQSteps; ++kk) {
+                    const uint4 v = rawq[r][kk];
+                    if constexpr (C::lowbit)
+                        qf[r][kk] = __builtin_bit_cast(f16x8, make_uint4(bf16x2_to_f16x2(v.x), bf16x2_to_f16x2(v.y),
+                                                                         bf16x2_to_f16x2(v.z), bf16x2_to_f16x2(v.w)));
+                    else
+                        qf[r][kk] = __builtin_bit_cast(bf16x8, v);
+                    // 16 rows: kept in accumulation registers, which the score
+                    // products read directly as their B operand
+                    if constexpr (kR == 16) asm volatile("" : "+a"(qf[r][kk]));
                 }
             }
         };
 
-        if (n_tiles == 0) return;
-#pragma unroll
-        for (int j = 0; j < C::D; ++j) issue_tile(j);
-
-        // online softmax of one tile's scores (lane: tokens 4g+v of row li):
-        // masks, moves the reference (rescaling the accumulators, which hold
-        // every earlier tile) when needed, returns the weights
-        auto softmax = [&](int it, f32x4 s, float p[4]) __attribute__((always_inline)) {
+        // online softmax of one tile's scores s: masks, moves the reference
+        // (rescaling the accumulators, which hold every earlier tile) when
+        // needed, returns the weights.  Score v of a lane is token tok_of(v).
+        auto tok_of = [&](int v) {
+            return kR == 16 ? 16 * (v >> 2) + 4 * g + (v & 3) : 8 * half + v;
+        };
+        auto softmax = [&](int it, float (&s)[kScores], float (&p)[kScores]) __attribute__((always_inline)) {
             const int t0 = t_begin + it * kTok;
+            // rows see every key of the tile except in the last tile of the range,
+            // the tile holding the newest key, or the one with the last sink token
+            // (wave-uniform test)
+            bool edge = t0 + kTok > full_lim;
+            if constexpr (kProt) edge = edge || t0 < t_lo;
+            if (edge) {
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int t = t0 + 4 * g + v;
-                bool ok = t < lim;
-                if constexpr (kProt) ok = ok && t >= t_lo;
-                s[v] = ok ? s[v] : -INFINITY;
+                for (int v = 0; v < kScores; ++v) {
+                    const int t = t0 + tok_of(v);
+                    bool ok = t < lim;
+                    if constexpr (kProt) ok = ok && t >= t_lo;
+                    s[v] = ok ? s[v] : -INFINITY;
+                }
             }
-            const float mr = max4(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])));
+            float mr = s[0];
+#pragma unroll
+            for (int v = 1; v < kScores; ++v) mr = fmaxf(mr, s[v]);
+            mr = kR == 16 ? max4(mr) : max2(mr);
             const float mt = mr * a.scale_log2;
             m_true = fmaxf(m_true, mt);
             if (m_ref == -INFINITY) m_ref = mt;
@@ -418,220 +501,451 @@ __global__ __launch_bounds__(64) void narrow_kernel(DecodeArgs a) {
                 const float alpha = m_new == m_ref ? 1.0f : __builtin_amdgcn_exp2f(m_ref - m_new);
                 m_ref = m_new;
                 l_run *= alpha;
+                if constexpr (kR == 16) {
 #pragma unroll
-                for (int m = 0; m < 32; ++m) acc[m] *= alpha;
+                    for (int m = 0; m < kAccs; ++m) acc[m] *= alpha;
+                } else {
+                    // in place: the accumulators fill the accumulation registers (the
+                    // score products between them and here cover their latency)
+#pragma unroll
+                    for (int m = 0; m < kAccs; ++m)
+#pragma unroll
+                        for (int v = 0; v < kAccLen; ++v) {
+                            float t;
+                            asm volatile("v_accvgpr_read_b32 %1, %0\n\tv_mul_f32 %1, %1, %2\n\tv_accvgpr_write_b32 %0, %1"
+                                         : "+a"(acc[m][v]), "=&v"(t)
+                                         : "v"(alpha));
+                        }
+                }
             }
             const float nref = m_ref == -INFINITY ? 0.0f : -m_ref;
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                p[v] = __builtin_amdgcn_exp2f(fmaf(s[v], a.scale_log2, nref));
-                // the normalizer sums the weights the aggregation uses: fp16-rounded
-                // (low-bit), bf16-rounded (the BF16 cache), or to 16 significant bits
-                // (protected rows, a bf16 pair)
-                if constexpr (C::lowbit) p[v] = static_cast<float>(static_cast<_Float16>(p[v]));
-                else if constexpr (!kRing) p[v] = static_cast<float>(static_cast<__bf16>(p[v]));
-                l_run += p[v];
-            }
+            for (int v = 0; v < kScores; ++v) p[v] = __builtin_amdgcn_exp2f(fmaf(s[v], a.scale_log2, nref));
         };
 
         if constexpr (C::lowbit) {
             // Software pipeline: step it computes the scores of tile it (its
             // operands dequantized in registers) interleaved with the aggregation
-            // of tile it-1 (read transposed from the fp16 tile); once the
-            // aggregation's reads are done, tile it's content channels replace
-            // tile it-1's in the fp16 tile.
-            uint8_t* tile = smem + C::NS * C::stage_bytes;
-            const uint8_t* vbase = tile + 16 * f16_row(4 * g + (li >> 2)) + 8 * (li & 3);
-            uint32_t words[kQSteps];
-            uint4 mc0, mc1;
-            uint32_t rmw = 0;
-            auto read_stage = [&](const uint8_t* st) __attribute__((always_inline)) {
-#pragma unroll
-                for (int kk = 0; kk < kQSteps; ++kk) {
-                    if (kk >= 16)
-                        words[kk] = *reinterpret_cast<const uint32_t*>(st + 16 * (C::u_rc + 16 * (kk - 16) + li) + 4 * g);
-                    else if constexpr (C::cbits == 4)
-                        words[kk] = *reinterpret_cast<const uint32_t*>(st + 16 * (16 * kk + li) + 4 * g);
-                    else    // channels 32 kk + 8 g ..: word 2 kk + g / 2, upper or lower 8 (sh0)
-                        words[kk] = *reinterpret_cast<const uint32_t*>(st + 16 * (16 * (kk >> 1) + li) + 8 * (kk & 1) +
-                                                                       4 * (g >> 1));
+            // of tile it-1 (read transposed from the fp16 tile).
+            int pg = t_begin / P, po = t_begin % P;     // page and offset of the tile to load next
+            int pid_base = pg;                          // lane l holds the id of page pid_base + l
+            int pids = bt[min(pid_base + lane, a.max_pages - 1)];
+
+            // One tile's packed bytes in registers, per 16-token block: content
+            // codes (slice j: channels 128 j + 32 g .. +32), RoPE codes (channels
+            // 16 g .. +16) and the metadata of the lane's groups 2 j + g / 2 (paper
+            // storage: the token's whole record).
+            using CodeT = std::conditional_t<C::cbits == 4, u32x4, u32x2>;
+            CodeT cw[kNB][4];
+            u32x2 rw[kNB];
+            uint32_t mw[kNB][4], rmw[kNB];
+            u32x4 pm0[kNB], pm1[kNB];
+            const uint8_t* page = nullptr;
+            uint32_t oc[kNB], orc[kNB], om[kNB], orm[kNB];
+            // page and lane offsets of tile j, and the cursor's move to the next
+            // tile (past the end it stays on the last, which is then read again)
+            auto locate = [&](int j) __attribute__((always_inline)) {
+                const int t0 = t_begin + min(j, n_tiles - 1) * kTok;
+                const int last = min(t_end - t0, kTok) - 1;     // tokens past it re-read it
+                if (pg - pid_base == 64) {
+                    pid_base = pg;
+                    pids = load_waited(bt, min(pid_base + lane, a.max_pages - 1));
                 }
-                mc0 = *reinterpret_cast<const uint4*>(st + 16 * (C::u_mc + li));
-                mc1 = *reinterpret_cast<const uint4*>(st + 16 * (C::u_mc + 16 + li));
-                if constexpr (!C::pmeta) rmw = *reinterpret_cast<const uint32_t*>(st + 16 * C::u_mr + 4 * li);
-            };
-            // dequantization constants of the group holding k-step kk (its
-            // scale, 1024 + zero, and the zero offsets of the in-place extraction)
-            struct Gm { f16x2 zz, ss, zo[3]; };
-            auto group_meta = [&](int kk) __attribute__((always_inline)) {
-                Gm m;
-                if (kk >= 16) {
-                    if constexpr (C::pmeta) pmeta_to_f16(__uint_as_float(mc1.z), mc1.w & 0xFFu, m.zz, m.ss);
-                    else meta_to_f16(rmw, m.zz, m.ss);
-                } else {
-                    const int grp = kk >> 1;
-                    if constexpr (C::pmeta) {
-                        const uint32_t sw = grp < 4 ? (grp < 2 ? mc0.x : mc0.y) : (grp < 6 ? mc0.z : mc0.w);
-                        const uint32_t sbits = (sw >> (16 * (grp & 1))) & 0xFFFFu;
-                        const uint32_t zw = grp < 4 ? mc1.x : mc1.y;
-                        pmeta_to_f16(__uint_as_float(sbits << 16), (zw >> (8 * (grp & 3))) & 0xFFu, m.zz, m.ss);
-                    } else {
-                        const uint32_t mw = grp < 4 ? (grp < 2 ? (grp == 0 ? mc0.x : mc0.y) : (grp == 2 ? mc0.z : mc0.w))
-                                                    : (grp < 6 ? (grp == 4 ? mc1.x : mc1.y) : (grp == 6 ? mc1.z : mc1.w));
-                        meta_to_f16(mw, m.zz, m.ss);
+                int pid = __builtin_amdgcn_readlane(pids, pg - pid_base);
+                pid = min(max(pid, 0), static_cast<int>(a.num_pages - 1));
+                page = a.cache + static_cast<uint64_t>(static_cast<uint32_t>(pid)) * static_cast<uint32_t>(a.g.page_bytes);
+#pragma unroll
+                for (int nb = 0; nb < kNB; ++nb) {
+                    const uint32_t t = static_cast<uint32_t>(po + min(16 * nb + li, last));
+                    oc[nb] = t * C::cc + (C::cbits == 4 ? 16 : 8) * g;
+                    orc[nb] = static_cast<uint32_t>(a.g.off_cr) + t * 32 + 8 * g;
+                    om[nb] = static_cast<uint32_t>(a.g.off_mc) + t * 32 + (C::pmeta ? 0 : 4 * (g >> 1));
+                    orm[nb] = static_cast<uint32_t>(a.g.off_mr) + t * 4;
+                }
+                if (j < n_tiles - 1) {
+                    po += kTok;
+                    if (po == P) {
+                        po = 0;
+                        ++pg;
                     }
+                }
+            };
+            auto load_slice = [&](int j) __attribute__((always_inline)) {
+#pragma unroll
+                for (int nb = 0; nb < kNB; ++nb) {
+                    cw[nb][j] = load_nt<CodeT>(page, oc[nb] + (C::cbits == 4 ? 64 : 32) * j);
+                    if constexpr (!C::pmeta) mw[nb][j] = load_nt<uint32_t>(page, om[nb] + 8 * j);
+                }
+            };
+            auto load_rope = [&]() __attribute__((always_inline)) {
+#pragma unroll
+                for (int nb = 0; nb < kNB; ++nb) {
+                    rw[nb] = load_nt<u32x2>(page, orc[nb]);
+                    if constexpr (C::pmeta) {
+                        pm0[nb] = load_nt<u32x4>(page, om[nb]);
+                        pm1[nb] = load_nt<u32x4>(page, om[nb] + 16);
+                    } else {
+                        rmw[nb] = load_nt<uint32_t>(page, orm[nb]);
+                    }
+                }
+            };
+
+            // dequantization constants of slice j (j = 4: the RoPE group) of a
+            // block's token: scale, 1024 + zero, and the zero offsets of the
+            // in-place extraction
+            struct Gm { f16x2 zz, ss, zo[3]; };
+            auto group_meta = [&](int nb, int j) __attribute__((always_inline)) {
+                Gm m;
+                if constexpr (C::pmeta) {
+                    if (j == 4) {
+                        pmeta_to_f16(__uint_as_float(pm1[nb][2]), pm1[nb][3] & 0xFFu, m.zz, m.ss);
+                    } else {
+                        // group 2 j + g / 2: scale in half g / 2 of word j, zero in byte 2 j + g / 2
+                        const uint32_t sbits = (pm0[nb][j] >> (16 * (g >> 1))) << 16;
+                        const uint32_t z = ((j < 2 ? pm1[nb][0] : pm1[nb][1]) >> (16 * (j & 1) + 8 * (g >> 1))) & 0xFFu;
+                        pmeta_to_f16(__uint_as_float(sbits), z, m.zz, m.ss);
+                    }
+                } else {
+                    meta_to_f16(j == 4 ? rmw[nb] : mw[nb][j], m.zz, m.ss);
                 }
                 zero_offsets(m.zz, m.zo);
                 return m;
             };
-            auto dq = [&](int kk, const Gm& m) __attribute__((always_inline)) {
-                if (kk >= 16) return dequant8<4>(words[kk], 0, m.zz, m.zo, m.ss);
-                return dequant8<C::cbits>(words[kk], C::cbits == 4 ? 0 : 8 * (g & 1), m.zz, m.zo, m.ss);
+            // k-step kk's channels of every block (the three operations per pair,
+            // operation by operation over all blocks: a packed operation that
+            // reads the one just before it costs a wait state)
+            auto dq = [&](int kk, const Gm (&m)[kNB], f16x8 (&o)[kNB]) __attribute__((always_inline)) {
+                DqWord x[kNB];
+#pragma unroll
+                for (int nb = 0; nb < kNB; ++nb) {
+                    const int j = (kk >> 2) & 3, wd = kk & 3;
+                    if (kk >= 16) x[nb].template extract<4>(rw[nb][kk & 1], 0);
+                    else if constexpr (C::cbits == 4) x[nb].template extract<4>(cw[nb][j][wd], 0);
+                    else x[nb].template extract<2>(cw[nb][j][wd >> 1], 8 * (wd & 1));
+                }
+#pragma unroll
+                for (int nb = 0; nb < kNB; ++nb) {
+                    if (kk >= 16 || C::cbits == 4) x[nb].template center<4>(m[nb].zz, m[nb].zo);
+                    else x[nb].template center<2>(m[nb].zz, m[nb].zo);
+                }
+#pragma unroll
+                for (int nb = 0; nb < kNB; ++nb) o[nb] = x[nb].scaled(m[nb].ss);
             };
-            float p[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-            constexpr int kVAhead = 8;
-            s16x4 vb[kVAhead];
-            auto vread = [&](int m) {
-                return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(vbase + 32 * m));
+
+            // the page ids' round trip overlaps the query loads' issue
+            read_q();
+            __builtin_amdgcn_sched_barrier(0);
+            locate(0);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) load_slice(j);
+            load_rope();
+            __builtin_amdgcn_sched_barrier(0);
+            set_q();
+
+            uint8_t* tile = smem;
+            const uint8_t* vbase = tile + tr_lane_off(f16_row);
+            constexpr int kVOff = kR == 16 ? 16 * (f16_row(16) - f16_row(0)) : 16 * (f16_row(4) - f16_row(0));
+            static_assert(f16_row(31) - f16_row(15) == f16_row(16) - f16_row(0) && f16_row(15) - f16_row(11) == f16_row(4),
+                          "second transposing read at a fixed offset");
+            f16x8 pb{};                                  // weights of the previous tile (P^T operand)
+            // k-steps of slice j store channels of the slice's eight 16-channel
+            // blocks, so their transposing reads come 8 blocks ahead
+            constexpr int kVAhead = kAccs / 4;
+            f16x8 vb[kVAhead];
+            auto vread = [&](int m) __attribute__((always_inline)) {
+                const i16x4 v0 = tr_read(vbase + tr_imm(m));
+                const i16x4 v1 = tr_read(vbase + tr_imm(m) + kVOff);
+                return __builtin_bit_cast(f16x8, __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
             };
-            auto pv = [&](int m, f16x4 pbh) __attribute__((always_inline)) {
-                acc[m] = __builtin_amdgcn_mfma_f32_16x16x16f16(__builtin_bit_cast(f16x4, vb[m % kVAhead]), pbh, acc[m],
-                                                               0, 0, 0);
-                if (m + kVAhead < 32) vb[m % kVAhead] = vread(m + kVAhead);
+            auto pv = [&](int m) __attribute__((always_inline)) {
+                if constexpr (kR == 16)
+                    acc[m] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vb[m % kVAhead], pb, acc[m], 0, 0, 0);
+                else
+                    acc[m] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vb[m % kVAhead], pb, acc[m], 0, 0, 0);
+                if (m + kVAhead < kAccs) vb[m % kVAhead] = vread(m + kVAhead);
             };
-            // one step: scores of tile it (QK) and aggregation of tile it-1 (PV).
-            // Tile it's content channels 32 kk + 8 g .. +8 (channel blocks 2 kk and
-            // 2 kk + 1) replace tile it-1's as soon as they are dequantized: the
-            // transposing reads of those blocks were issued before (in the previous
-            // k-steps, or before the loop), and LDS serves one wave's accesses in
-            // the order they are issued.
+            // one step: scores of tile it (QK), the loads of tile it+1, and the
+            // aggregation of tile it-1 (PV).  Tile it's content channels replace
+            // tile it-1's as soon as they are dequantized: the transposing reads of
+            // those blocks were issued before, and LDS serves one wave's accesses
+            // in the order they are issued.
             auto step = [&](int it, auto QK, auto PV) __attribute__((always_inline)) {
                 constexpr bool kQK = decltype(QK)::value, kPV = decltype(PV)::value;
-                const f16x4 pbh = {static_cast<_Float16>(p[0]), static_cast<_Float16>(p[1]),
-                                   static_cast<_Float16>(p[2]), static_cast<_Float16>(p[3])};
-                f32x4 s = f32x4{};
-                // tile it's code words were read at the end of the previous step;
-                // its staging slot is free (the slot of tile it + D held tile it - 1)
-                if constexpr (kQK) issue_tile(it + C::D);
+                f32x4 s[kNB][kNR];
+#pragma unroll
+                for (int nb = 0; nb < kNB; ++nb)
+#pragma unroll
+                    for (int r = 0; r < kNR; ++r) s[nb][r] = f32x4{};
+                if constexpr (kQK) locate(it + 1);
                 if constexpr (kPV) {
 #pragma unroll
                     for (int m = 0; m < kVAhead; ++m) vb[m] = vread(m);
                 }
                 __builtin_amdgcn_sched_barrier(0);
-                // the dequantization runs one k-step ahead of the score product,
-                // so that vector work separates the products (each 16 cycles on the
-                // matrix unit) instead of issuing them back to back
-                Gm gm;
-                f16x8 kv_next;
+                // the dequantization runs one k-step ahead of the score products,
+                // so that vector work separates the products
+                Gm gm[kNB];
+                f16x8 kv_next[kNB];
                 if constexpr (kQK) {
-                    gm = group_meta(0);
-                    kv_next = dq(0, gm);
+#pragma unroll
+                    for (int nb = 0; nb < kNB; ++nb) gm[nb] = group_meta(nb, 0);
+                    dq(0, gm, kv_next);
                 }
 #pragma unroll
                 for (int kk = 0; kk < kQSteps; ++kk) {
-                    f16x8 kv;
+                    f16x8 kv[kNB];
                     if constexpr (kQK) {
-                        kv = kv_next;
-                        s = __builtin_amdgcn_mfma_f32_16x16x32_f16(kv, qf[kk], s, 0, 0, 0);
-                    }
-                    if constexpr (kPV) {
-                        if (kk < 16) pv(2 * kk, pbh);
-                    }
-                    if constexpr (kQK) {
-                        if (kk + 1 < kQSteps) {
-                            if (((kk + 1) & 1) == 0) gm = group_meta(kk + 1);
-                            kv_next = dq(kk + 1, gm);
+#pragma unroll
+                        for (int nb = 0; nb < kNB; ++nb) {
+                            kv[nb] = kv_next[nb];
+#pragma unroll
+                            for (int r = 0; r < kNR; ++r) {
+                                if constexpr (kR == 16)
+                                    s[nb][r] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kv[nb], qf[r][kk], s[nb][r], 0, 0, 0);
+                                else
+                                    score_mfma(s[nb][r], kv[nb], qf[r][kk], kk == 0);
+                            }
                         }
                     }
                     if constexpr (kPV) {
-                        if (kk < 16) pv(2 * kk + 1, pbh);
+                        if (kk < 16) {
+                            pv(kAccs / 16 * kk);
+                            if constexpr (kAccs == 32) pv(2 * kk + 1);
+                        }
                     }
                     if constexpr (kQK) {
-                        if (kk < 16) *reinterpret_cast<f16x8*>(tile + 16 * (f16_row(li) + 4 * kk + g)) = kv;
+                        if (kk + 1 < kQSteps) {
+#pragma unroll
+                            for (int nb = 0; nb < kNB; ++nb)
+                                if (((kk + 1) & 3) == 0) gm[nb] = group_meta(nb, (kk + 1) >> 2);
+                            dq(kk + 1, gm, kv_next);
+                        }
+                        // slice (kk + 1) / 4 is used up: its registers take the next tile's
+                        if (kk < 16 && ((kk + 1) & 3) == 3) load_slice((kk + 1) >> 2);
+                        if (kk + 1 == kQSteps - 1) load_rope();
+#pragma unroll
+                        for (int nb = 0; nb < kNB; ++nb)
+                            if (kk < 16)
+                                *reinterpret_cast<f16x8*>(tile + 16 * (f16_row(16 * nb + li) + 16 * (kk >> 2) + 4 * g + (kk & 3))) = kv[nb];
                     }
                     if constexpr (kQK && kPV) {
                         if (kk < 16) {
-                            // product, 5 vector, product, 5 vector, product, the rest
-                            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                            __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);
-                            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                            __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);
-                            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                            // products spread over the k-step's vector work
+                            constexpr int kProducts = kNB * kNR + kAccs / 16;
+                            constexpr int kGap = kR == 16 ? 7 : 5;
+#pragma unroll
+                            for (int i = 0; i < kProducts; ++i) {
+                                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                                __builtin_amdgcn_sched_group_barrier(0x002, kGap, 0);
+                            }
                         }
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 if constexpr (kQK) {
-                    if (it + 1 < n_tiles) {
-                        // tile it+1 has landed: its code words are read while the
-                        // softmax runs
-                        wait_loads<(C::D - 1) * C::loads>();
-                        read_stage(slot_base(it + 1));
+                    float sc[kScores], p[kScores];
+                    if constexpr (kR == 16) {
+#pragma unroll
+                        for (int v = 0; v < kScores; ++v) {
+                            sc[v] = s[(v >> 2) % kNB][0][v & 3];
+                            // out of the accumulation registers once, before the branches
+                            asm volatile("" : "+v"(sc[v]));
+                        }
+                    } else {
+                        score_ready(s[0][0], s[0][kNR - 1]);
+                        // lanes of row block 0 and 1 exchange, so that lane l holds row
+                        // l % 32: {a0 b0 a2 b2} tokens 8 half + v, {a1 b1 a3 b3} + 4
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            const auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(s[0][0][v]),
+                                                                            __float_as_uint(s[0][kNR - 1][v]), false, false);
+                            sc[v] = __uint_as_float(x[0]);
+                            sc[4 + v] = __uint_as_float(x[1]);
+                        }
                     }
-                    softmax(it, s, p);
+                    softmax(it, sc, p);
+                    uint32_t pw[4];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        // the normalizer sums the fp16 weights the aggregation uses
+                        pw[q] = pack_f16x2(p[2 * q], p[2 * q + 1]);
+                        l_run = __builtin_amdgcn_fdot2(__builtin_bit_cast(f16x2, pw[q]), f16x2{1.0f16, 1.0f16}, l_run, false);
+                    }
+                    pb = __builtin_bit_cast(f16x8, make_uint4(pw[0], pw[1], pw[2], pw[3]));
                 }
             };
-            wait_loads<(C::D - 1) * C::loads>();
-            read_stage(slot_base(0));
             step(0, std::true_type{}, std::false_type{});
             for (int it = 1; it < n_tiles; ++it) step(it, std::true_type{}, std::true_type{});
             step(n_tiles, std::false_type{}, std::true_type{});
         } else {
             // raw bf16 rows: both products read the staged tile directly
+            read_q();
+            int st_pg = t_begin / P, st_po = t_begin % P, pid_pg = -1, pid = 0;   // next tile to stage
+            auto slot_base = [&](int j) { return smem + slot_offset(j, kBfSlots, kBfTileBytes); };
+            auto issue_tile = [&](int j) __attribute__((always_inline)) {
+                const int t0 = t_begin + min(j, n_tiles - 1) * kTok;   // past the end: the last tile again
+                const int nvalid = min(t_end - t0, kTok);
+                const uint32_t lds = lds_addr(slot_base(j));
+                if constexpr (kRing) {
+                    auto row_start = [&](int tok) {
+                        const int v = t0 + tok;
+                        const int x = ring_q0 + (v - ring_nsink);       // < 2 * recent
+                        const int r = v < ring_nsink ? v : a.sink + (x >= a.recent ? x - a.recent : x);
+                        return min(r, ring_rows - 1) * 1152;
+                    };
+#pragma unroll
+                    for (int k = 0; k < kBfLoads; ++k) stage_narrow_bf16(k, ring_base, row_start, nvalid, lds, lane);
+                } else {
+                    // tiles are issued in order; a 16-token tile never crosses a page
+                    // (t_begin and the page size are multiples of 32), and the page
+                    // id is fetched once per page
+                    if (st_pg != pid_pg) {
+                        pid = load_page_id(bt, st_pg);
+                        pid = min(max(pid, 0), static_cast<int>(a.num_pages - 1));
+                        pid_pg = st_pg;
+                    }
+                    const uint8_t* page = a.cache + static_cast<int64_t>(pid) * a.g.page_bytes;
+                    const int po = st_po;
+                    if (j < n_tiles - 1) {
+                        st_po += kTok;
+                        if (st_po == P) {
+                            st_po = 0;
+                            ++st_pg;
+                        }
+                    }
+                    auto row_start = [&](int tok) { return (po + tok) * 1152; };
+#pragma unroll
+                    for (int k = 0; k < kBfLoads; ++k) stage_narrow_bf16(k, page, row_start, nvalid, lds, lane);
+                }
+            };
+            issue_tile(0);
+            set_q();
             for (int it = 0; it < n_tiles; ++it) {
                 // tile it has landed and every LDS access of the previous step is
-                // done; then stage tile it+D into the slot tile it-1 used
-                wait_loads<(C::D - 1) * C::loads>();
-                issue_tile(it + C::D);
+                // done; then stage tile it+1 into the slot tile it-1 used
+                wait_loads<0>();
+                issue_tile(it + 1);
                 const uint8_t* st = slot_base(it);
-                bf16x8 kv[kQSteps];
+                f32x4 s[kNR];
 #pragma unroll
-                for (int kk = 0; kk < kQSteps; ++kk)
-                    kv[kk] = *reinterpret_cast<const bf16x8*>(st + 16 * (bf_row(li) + 4 * kk + g));
-                f32x4 s = f32x4{};
+                for (int r = 0; r < kNR; ++r) s[r] = f32x4{};
+                constexpr int kKAhead = kR == 16 ? kQSteps : 6;
+                bf16x8 kv[kKAhead];
+                auto kread = [&](int kk) __attribute__((always_inline)) {
+                    return *reinterpret_cast<const bf16x8*>(st + 16 * (bf_row(li) + 4 * kk + g));
+                };
 #pragma unroll
-                for (int kk = 0; kk < kQSteps; ++kk) s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kv[kk], qf[kk], s, 0, 0, 0);
-                float p[4];
-                softmax(it, s, p);
-                // aggregation: O^T[16 channels][16 rows] += V^T . P^T per block,
-                // transposing reads eight blocks ahead of the products
-                const uint8_t* vbase = st + 16 * bf_row(4 * g + (li >> 2)) + 8 * (li & 3);
-                constexpr int kVAhead = 8;
-                s16x4 vb[kVAhead];
+                for (int kk = 0; kk < kKAhead; ++kk) kv[kk] = kread(kk);
 #pragma unroll
-                for (int m = 0; m < kVAhead; ++m) vb[m] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(vbase + 32 * m));
-                // protected rows: the weights to 16 significant bits, bf16(w) and the
-                // bf16 rounding of the exact residual w - bf16(w), two products per
-                // block; the BF16 cache: the bf16 weights alone (already rounded)
-                const uint32_t h01 = pack_bf16x2(p[0], p[1]), h23 = pack_bf16x2(p[2], p[3]);
-                const s16x4 pbb = __builtin_bit_cast(s16x4, make_uint2(h01, h23));
-                const s16x4 pbl = __builtin_bit_cast(
-                    s16x4, make_uint2(pack_bf16x2(p[0] - __uint_as_float(h01 << 16), p[1] - __uint_as_float(h01 & 0xFFFF0000u)),
-                                      pack_bf16x2(p[2] - __uint_as_float(h23 << 16), p[3] - __uint_as_float(h23 & 0xFFFF0000u))));
+                for (int kk = 0; kk < kQSteps; ++kk) {
 #pragma unroll
-                for (int m = 0; m < 32; ++m) {
-                    acc[m] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vb[m % kVAhead], pbb, acc[m], 0, 0, 0);
-                    if constexpr (kRing)
-                        acc[m] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vb[m % kVAhead], pbl, acc[m], 0, 0, 0);
-                    if (m + kVAhead < 32)
-                        vb[m % kVAhead] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(vbase + 32 * (m + kVAhead)));
+                    for (int r = 0; r < kNR; ++r) {
+                        if constexpr (kR == 16)
+                            s[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kv[kk % kKAhead], qf[r][kk], s[r], 0, 0, 0);
+                        else
+                            score_mfma(s[r], kv[kk % kKAhead], qf[r][kk], kk == 0);
+                    }
+                    if (kk + kKAhead < kQSteps) kv[kk % kKAhead] = kread(kk + kKAhead);
+                }
+                float sc[kScores], p[kScores];
+                if constexpr (kR == 16) {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) sc[v] = s[0][v];
+                } else {
+                    score_ready(s[0], s[kNR - 1]);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(s[0][v]),
+                                                                        __float_as_uint(s[kNR - 1][v]), false, false);
+                        sc[v] = __uint_as_float(x[0]);
+                        sc[4 + v] = __uint_as_float(x[1]);
+                    }
+                }
+                softmax(it, sc, p);
+                // The weights as bf16 (the BF16 cache; the normalizer sums the
+                // rounded weights), or over protected rows to 16 significant bits:
+                // bf16(w) and the bf16 rounding of the exact residual w - bf16(w),
+                // two products per block.
+                uint32_t ph[kScores / 2], pl[kScores / 2];
+#pragma unroll
+                for (int q = 0; q < kScores / 2; ++q) {
+                    ph[q] = pack_bf16x2(p[2 * q], p[2 * q + 1]);
+                    const float h0 = __uint_as_float(ph[q] << 16), h1 = __uint_as_float(ph[q] & 0xFFFF0000u);
+                    pl[q] = pack_bf16x2(p[2 * q] - h0, p[2 * q + 1] - h1);
+                    l_run += kRing ? p[2 * q] : h0;
+                    l_run += kRing ? p[2 * q + 1] : h1;
+                }
+                // aggregation, transposing reads eight (16 rows) or four blocks
+                // ahead of the products
+                const uint8_t* vbase = st + tr_lane_off(bf_row);
+                constexpr int kVAhead = kR == 16 ? 8 : 4;
+                if constexpr (kR == 16) {
+                    s16x4 vb[kVAhead];
+                    const s16x4 pbh = __builtin_bit_cast(s16x4, make_uint2(ph[0], ph[1]));
+                    const s16x4 pbl = __builtin_bit_cast(s16x4, make_uint2(pl[0], pl[1]));
+#pragma unroll
+                    for (int m = 0; m < kVAhead; ++m) vb[m] = tr_read(vbase + tr_imm(m));
+#pragma unroll
+                    for (int m = 0; m < kAccs; ++m) {
+                        acc[m] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vb[m % kVAhead], pbh, acc[m], 0, 0, 0);
+                        if constexpr (kRing)
+                            acc[m] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vb[m % kVAhead], pbl, acc[m], 0, 0, 0);
+                        if (m + kVAhead < kAccs) vb[m % kVAhead] = tr_read(vbase + tr_imm(m + kVAhead));
+                    }
+                } else {
+                    constexpr int kVOff = 16 * (bf_row(4) - bf_row(0));
+                    static_assert(bf_row(15) - bf_row(11) == bf_row(4), "second transposing read at a fixed offset");
+                    auto vread = [&](int m) __attribute__((always_inline)) {
+                        const i16x4 v0 = tr_read(vbase + tr_imm(m));
+                        const i16x4 v1 = tr_read(vbase + tr_imm(m) + kVOff);
+                        return __builtin_bit_cast(bf16x8, __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
+                    };
+                    bf16x8 vb[kVAhead];
+                    constexpr int n = kScores / 2;
+                    const bf16x8 pbh = __builtin_bit_cast(bf16x8, make_uint4(ph[0], ph[1], ph[2 % n], ph[3 % n]));
+                    const bf16x8 pbl = __builtin_bit_cast(bf16x8, make_uint4(pl[0], pl[1], pl[2 % n], pl[3 % n]));
+#pragma unroll
+                    for (int m = 0; m < kVAhead; ++m) vb[m] = vread(m);
+#pragma unroll
+                    for (int m = 0; m < kAccs; ++m) {
+                        acc[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vb[m % kVAhead], pbh, acc[m], 0, 0, 0);
+                        if constexpr (kRing)
+                            acc[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vb[m % kVAhead], pbl, acc[m], 0, 0, 0);
+                        if (m + kVAhead < kAccs) vb[m % kVAhead] = vread(m + kVAhead);
+                    }
                 }
             }
+            // no direct-to-LDS load may outlive the wave's LDS
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         }
-        // no direct-to-LDS load may outlive the workgroup's LDS
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     };
 
+    // Part `wave` of kW of n list entries from u0: an equal share, rounded up.
+    auto part = [&](int& u0, int& u1) {
+        if constexpr (kW > 1) {
+            const int n = max(u1 - u0, 0), per = (n + kW - 1) / kW;
+            u1 = min(u0 + (wave + 1) * per, u0 + n);
+            u0 = min(u0 + wave * per, u1);
+        }
+    };
     if constexpr (!kProt) {
         int t_begin = 0, t_end = L;
         if (a.split_tokens != 0) {
             t_begin = max(split * a.split_tokens, 0);
             t_end = min(split * a.split_tokens + a.split_tokens, L);
         }
+        if constexpr (kW > 1) {
+            // 32-token units (t_begin is a multiple of 32)
+            int u0 = t_begin / 32, u1 = max((t_end + 31) / 32, u0);
+            part(u0, u1);
+            t_begin = 32 * u0;
+            t_end = min(32 * u1, t_end);
+        }
         const int lim = row_ok ? min(L - a.s_q + qi + 1, t_end) : t_begin;
+        const int full_lim = min(L - a.s_q + 1, t_end);
         if (a.new_c != nullptr)
             narrow_append<KIND, false>(a, b, L, [&](int pos) { return pos >= t_begin && pos < t_end; }, lane);
-        run(std::integral_constant<int, KIND>{}, std::false_type{}, t_begin, t_end, t_begin, lim);
+        run(std::integral_constant<int, KIND>{}, std::false_type{}, t_begin, t_end, t_begin, lim, full_lim);
     } else {
         // the tile list of mla_plan_splits_protected (32-key list tiles)
         const int sink = a.sink, recent = a.recent;
@@ -645,6 +959,7 @@ __global__ __launch_bounds__(64) void narrow_kernel(DecodeArgs a) {
             u0 = split * (a.split_tokens / 32);
             u1 = min(u0 + a.split_tokens / 32, n_list);
         }
+        part(u0, u1);
         if constexpr (NCfg<KIND>::lowbit) {
             if (a.new_c != nullptr) {
                 // list tile of position p: a packed position by its tile (from the
@@ -659,13 +974,14 @@ __global__ __launch_bounds__(64) void narrow_kernel(DecodeArgs a) {
                 narrow_append<KIND, true>(a, b, L, reads, lane);
             }
         }
-        if (u0 < n_pk) {
+        if (u0 < min(u1, n_pk)) {
             const int tb = 32 * (pk0 + u0);
             const int te = min(32 * (pk0 + min(u1, n_pk)), L - recent);
             const int lim = row_ok ? min(L - a.s_q + qi + 1, te) : tb;
-            run(std::integral_constant<int, KIND>{}, std::false_type{}, tb, te, sink, lim);
+            const int full_lim = min(L - a.s_q + 1, te);
+            run(std::integral_constant<int, KIND>{}, std::false_type{}, tb, te, sink, lim, full_lim);
         }
-        if (u1 > n_pk) {
+        if (u1 > max(u0, n_pk)) {
             ring_rows = sink + recent;
             ring_nsink = min(sink, L);
             const int r0 = max(sink, L - recent);
@@ -677,54 +993,179 @@ __global__ __launch_bounds__(64) void narrow_kernel(DecodeArgs a) {
             const int vb = 32 * (max(u0, n_pk) - n_pk);
             const int ve = min(32 * (u1 - n_pk), n_prot);
             const int lim = row_ok ? min(below(L - a.s_q + qi + 1), ve) : vb;
-            run(std::integral_constant<int, KIND_BF16>{}, std::true_type{}, vb, ve, 0, lim);
+            const int full_lim = min(below(L - a.s_q + 1), ve);
+            run(std::integral_constant<int, KIND_BF16>{}, std::true_type{}, vb, ve, 0, lim, full_lim);
         }
     }
 
-    // ---- epilogue: this lane holds channels 16 m + 4 g .. +3 of row li
-    const float l_tot = sum4(l_run);
-    if (!row_ok) return;
-    const int64_t orow = qrow;
-    if (a.split_tokens == 0) {
-        const float inv = l_tot > 0.0f ? 1.0f / l_tot : 0.0f;
-        uint16_t* op = a.out + orow * kDc + 4 * g;
+    // ---- epilogue
+    const bool split_out = a.split_tokens != 0;
+    const int row0 = rb * kR;
+    const int last = min(kR, rows_total - row0) - 1;        // the block's last row
+    uint16_t* dst = split_out ? a.part_o + (static_cast<int64_t>(w) * rows_total + row0) * kDc
+                              : a.out + (static_cast<int64_t>(b) * rows_total + row0) * kDc;
+    float l_tot = kR == 16 ? sum4(l_run) : sum2(l_run);
+    float f_own = 1.0f;                 // this wave's share of the row is acc * f_own
+    if constexpr (kW > 1) {
+        // one reference for the row's kW parts: m_ref = max over the waves, the
+        // sums and accumulators of each moved to it (a part with no visible key
+        // has m_ref = -inf and weighs 0)
+        __shared__ float sh[3][kW][kR];
+        if (lane < kR) {
+            sh[0][wave][lane] = m_ref;
+            sh[1][wave][lane] = l_tot;
+            sh[2][wave][lane] = m_true;
+        }
+        __syncthreads();
+        const float own = m_ref;
 #pragma unroll
-        for (int m = 0; m < 32; ++m)
-            *reinterpret_cast<uint2*>(op + 16 * m) =
-                make_uint2(pack_bf16x2(acc[m][0] * inv, acc[m][1] * inv), pack_bf16x2(acc[m][2] * inv, acc[m][3] * inv));
-        if (a.lse != nullptr && g == 0)
-            a.lse[orow] = l_tot > 0.0f ? (m_ref + log2f(l_tot)) * kLn2 : -INFINITY;
-    } else {
-        const int64_t prow = (static_cast<int64_t>(w) * a.s_q + qi) * a.H + h;
-        const float f = m_true == -INFINITY ? 0.0f : exp2f(m_ref - m_true);
-        const float inv = l_tot > 0.0f ? 1.0f / l_tot : 0.0f;
-        uint16_t* op = a.part_o + prow * kDc + 4 * g;
+        for (int x = 0; x < kW; ++x) {
+            m_ref = fmaxf(m_ref, sh[0][x][lrow]);
+            m_true = fmaxf(m_true, sh[2][x][lrow]);
+        }
+        const float nref = m_ref == -INFINITY ? 0.0f : m_ref;
+        f_own = __builtin_amdgcn_exp2f(own - nref);
+        l_tot = 0.0f;
 #pragma unroll
-        for (int m = 0; m < 32; ++m)
-            *reinterpret_cast<uint2*>(op + 16 * m) =
-                make_uint2(pack_f16x2(acc[m][0] * inv, acc[m][1] * inv), pack_f16x2(acc[m][2] * inv, acc[m][3] * inv));
-        if (g == 0) {
-            a.part_m[prow] = m_true * kLn2;
-            a.part_s[prow] = l_tot * f;
+        for (int x = 0; x < kW; ++x) {
+            const float fx = __builtin_amdgcn_exp2f(sh[0][x][lrow] - nref);
+            l_tot += fx * sh[1][x][lrow];
         }
     }
+    const float inv = (l_tot > 0.0f ? 1.0f / l_tot : 0.0f) * f_own;
+    // channels of accumulator m, values 4 q .. 4 q + 3
+    auto channel = [&](int m, int q) {
+        if constexpr (kR == 16) return 16 * m + 4 * g;
+        const int x = 8 * (m >> 2) + (m & 3) + (q >= 2 ? 4 : 0);       // 16-channel block
+        return 16 * x + 8 * (q & 1) + 4 * half;
+    };
+    auto pack4 = [&](float x0, float x1, float x2, float x3) {
+        return split_out ? make_uint2(pack_f16x2(x0, x1), pack_f16x2(x2, x3))
+                         : make_uint2(pack_bf16x2(x0, x1), pack_bf16x2(x2, x3));
+    };
+    if constexpr (kW == 1) {
+        // the rows go out through LDS, one whole row (1 KiB) per store
+#pragma unroll
+        for (int m = 0; m < kAccs; ++m)
+#pragma unroll
+            for (int q = 0; q < kAccLen / 4; ++q)
+                *reinterpret_cast<uint2*>(smem + lrow * kOutPitch + 2 * channel(m, q)) =
+                    pack4(acc[m][4 * q] * inv, acc[m][4 * q + 1] * inv, acc[m][4 * q + 2] * inv, acc[m][4 * q + 3] * inv);
+        // (H is a multiple of 16, so at 16 rows every row exists; at 32 rows those
+        // past the end repeat the last one: a test per row would leave each row's
+        // LDS read waiting alone before its store)
+#pragma unroll
+        for (int i0 = 0; i0 < kR; i0 += 8) {
+            uint4 v[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                v[i] = *reinterpret_cast<const uint4*>(smem + min(i0 + i, last) * kOutPitch + 16 * lane);
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                *reinterpret_cast<uint4*>(dst + min(i0 + i, last) * kDc + 8 * lane) = v[i];
+        }
+    } else {
+        // fp32 rows of every wave in LDS, summed and stored by rows: wave x takes
+        // rows kR / kW x ..; 16 rows: all 512 channels at once, 32 rows: 256 at a time
+        constexpr int kRounds = kR == 16 ? 1 : 2;
+        constexpr int kPitch = merge_pitch(kR);
+        constexpr int kPer = 8 / kRounds;               // channels per lane
+#pragma unroll
+        for (int rd = 0; rd < kRounds; ++rd) {
+            if (rd > 0) __syncthreads();
+#pragma unroll
+            for (int m = 0; m < kAccs / kRounds; ++m)
+#pragma unroll
+                for (int q = 0; q < kAccLen / 4; ++q) {
+                    const AccT& x = acc[m + rd * kAccs / kRounds];
+                    *reinterpret_cast<float4*>(smem + lrow * kPitch + 4 * channel(m, q)) =
+                        make_float4(x[4 * q] * inv, x[4 * q + 1] * inv, x[4 * q + 2] * inv, x[4 * q + 3] * inv);
+                }
+            __syncthreads();
+            // kBatch rows' reads in flight together
+            constexpr int kBatch = 16 / (kW * kPer / 4);
+            static_assert(kR / kW % kBatch == 0, "whole batches");
+#pragma unroll
+            for (int i0 = 0; i0 < kR / kW; i0 += kBatch) {
+                float4 v[kBatch][kW][kPer / 4];
+#pragma unroll
+                for (int i = 0; i < kBatch; ++i)
+#pragma unroll
+                    for (int x = 0; x < kW; ++x)
+#pragma unroll
+                        for (int c = 0; c < kPer / 4; ++c)
+                            v[i][x][c] = *reinterpret_cast<const float4*>(
+                                smem_all + x * kLds + min(wave * (kR / kW) + i0 + i, last) * kPitch + 4 * (kPer * lane + 4 * c));
+#pragma unroll
+                for (int i = 0; i < kBatch; ++i) {
+                    uint16_t* op = dst + min(wave * (kR / kW) + i0 + i, last) * kDc + rd * (kDc / kRounds) + kPer * lane;
+#pragma unroll
+                    for (int c = 0; c < kPer / 4; ++c) {
+                        float4 o = v[i][0][c];
+#pragma unroll
+                        for (int x = 1; x < kW; ++x) {
+                            o.x += v[i][x][c].x;
+                            o.y += v[i][x][c].y;
+                            o.z += v[i][x][c].z;
+                            o.w += v[i][x][c].w;
+                        }
+                        *reinterpret_cast<uint2*>(op + 4 * c) = pack4(o.x, o.y, o.z, o.w);
+                    }
+                }
+            }
+        }
+        if (wave != 0) return;
+    }
+    if (!row_ok || lane >= kR) return;
+    if (!split_out) {
+        if (a.lse != nullptr)
+            a.lse[static_cast<int64_t>(b) * rows_total + row] = l_tot > 0.0f ? (m_ref + log2f(l_tot)) * kLn2 : -INFINITY;
+    } else {
+        const int64_t prow = static_cast<int64_t>(w) * rows_total + row;
+        const float f = m_true == -INFINITY ? 0.0f : exp2f(m_ref - m_true);
+        a.part_m[prow] = m_true * kLn2;
+        a.part_s[prow] = l_tot * f;
+    }
+}
+
+// Waves per work item.  A workgroup of kW waves takes kW of a unit's four SIMDs,
+// so 256 work items leave three waves in four idle at kW = 1 and 512 every
+// second one.  Measured (16 rows, one 256-token work item): 21.9, 15.7, 13.6 us at
+// 1, 2, 4 waves; 264 items of 128 tokens: 15.9, 14.0, 14.0 us; past 512 items the
+// extra waves only queue (520 items of 64 tokens: 16.1, 22.3, 27.8 us).
+template <int KIND, bool kProt, int kR>
+void launch_rows(const DecodeArgs& a, hipStream_t stream, const LaunchEvents& ev) {
+    const int64_t blocks = decode_workgroups(a.num_work, static_cast<int64_t>(a.s_q) * a.H, kR);
+    const dim3 grid(static_cast<unsigned>(blocks));
+    if (blocks <= kCus)
+        dispatch_decode(narrow_kernel<KIND, kProt, kR, 4>, grid, dim3(256), stream, ev, a);
+    else if (blocks <= 2 * kCus)
+        dispatch_decode(narrow_kernel<KIND, kProt, kR, 2>, grid, dim3(128), stream, ev, a);
+    else
+        dispatch_decode(narrow_kernel<KIND, kProt, kR, 1>, grid, dim3(64), stream, ev, a);
+}
+
+// One 32-row wave for 17 to 32 rows: each tile is dequantized once, where two
+// 16-row waves would do it twice (1.4 us per 16 tokens, against twice 1.5).
+template <int KIND, bool kProt>
+void launch_kind(const DecodeArgs& a, hipStream_t stream, const LaunchEvents& ev) {
+    if (a.s_q * a.H <= 16) launch_rows<KIND, kProt, 16>(a, stream, ev);
+    else launch_rows<KIND, kProt, kMaxRows>(a, stream, ev);
 }
 
 template <bool kProt>
 hipError_t launch(CacheKind kind, const DecodeArgs& a, hipStream_t stream) {
     if (a.num_work == 0) return hipSuccess;
     const LaunchEvents ev = take_launch_events();
-    static_assert(kNarrowThreads == 64, "one wave per workgroup");
-    const int64_t blocks = decode_workgroups(a.num_work, static_cast<int64_t>(a.s_q) * a.H, kRows);
-    const dim3 grid(static_cast<unsigned>(blocks)), block(kNarrowThreads);
+    static_assert(kNarrowThreads == 64 && kNarrowRowsPerBlock == 16, "the host checks the largest launch");
     switch (kind) {
-        case KIND_C4R4: dispatch_decode(narrow_kernel<KIND_C4R4, kProt>, grid, block, stream, ev, a); break;
-        case KIND_C2R4: dispatch_decode(narrow_kernel<KIND_C2R4, kProt>, grid, block, stream, ev, a); break;
-        case KIND_C4R4P: dispatch_decode(narrow_kernel<KIND_C4R4P, kProt>, grid, block, stream, ev, a); break;
-        case KIND_C2R4P: dispatch_decode(narrow_kernel<KIND_C2R4P, kProt>, grid, block, stream, ev, a); break;
+        case KIND_C4R4: launch_kind<KIND_C4R4, kProt>(a, stream, ev); break;
+        case KIND_C2R4: launch_kind<KIND_C2R4, kProt>(a, stream, ev); break;
+        case KIND_C4R4P: launch_kind<KIND_C4R4P, kProt>(a, stream, ev); break;
+        case KIND_C2R4P: launch_kind<KIND_C2R4P, kProt>(a, stream, ev); break;
         case KIND_BF16:
             if constexpr (kProt) return hipErrorInvalidValue;
-            else dispatch_decode(narrow_kernel<KIND_BF16, false>, grid, block, stream, ev, a);
+            else launch_kind<KIND_BF16, false>(a, stream, ev);
             break;
     }
     return hipGetLastError();
