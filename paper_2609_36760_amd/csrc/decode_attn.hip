@@ -83,8 +83,10 @@ using namespace kc;
 
 constexpr int kWaves = 4;
 constexpr int kThreads = 64 * kWaves;
-constexpr int kRowsPerBlock = 32 * kWaves;
-static_assert(kThreads == kDecodeThreads && kRowsPerBlock == kDecodeRowsPerBlock, "launch shape the host checks");
+// Query rows per workgroup: 128, or 64 when the four waves split each tile's
+// tokens in two halves (kTS = 2)
+constexpr int rows_per_block(int ts) { return 32 * kWaves / ts; }
+static_assert(kThreads == kDecodeThreads && rows_per_block(1) == kDecodeRowsPerBlock, "launch shape the host checks");
 constexpr int kTile = 32;                       // tokens per tile
 constexpr int kDc = 512;
 constexpr int kDk = 576;                        // d_c + d_r
@@ -181,6 +183,22 @@ __device__ __forceinline__ void mfma_v(f32x16& c, bf16x8 a, bf16x8 b, bool first
         asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(c) : "v"(a), "v"(b));
     else
         asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
+}
+// The 16-token score products of a token-split wave (kTS = 2).
+__device__ __forceinline__ void mfma_v(f32x4& c, f16x8 a, f16x8 b, bool first) {
+    if (first)
+        asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, 0" : "=&v"(c) : "v"(a), "v"(b));
+    else
+        asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
+}
+__device__ __forceinline__ void mfma_v(f32x4& c, bf16x8 a, bf16x8 b, bool first) {
+    if (first)
+        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=&v"(c) : "v"(a), "v"(b));
+    else
+        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
+}
+__device__ __forceinline__ void score_ready(f32x4& c0, f32x4& c1) {
+    asm volatile("s_nop 7\n\ts_nop 3" : "+v"(c0), "+v"(c1));
 }
 __device__ __forceinline__ void score_ready(f32x16& c) {
     asm volatile("s_nop 7\n\ts_nop 3" : "+v"(c));
@@ -589,9 +607,18 @@ __device__ __forceinline__ void append_in_launch_protected(const DecodeArgs& a, 
 // visible token enters one softmax in exactly one representation
 // (Appendix C.5, "BF16 protection and cache lifecycle", "Global attention
 // normalization").
-template <int KIND, bool kProt>
+//
+// Token split (kTS = 2, up to 64 query rows).  Waves 0 and 1 own row halves 0
+// and 1 of the first 16 tokens of every tile, waves 2 and 3 the same rows of the
+// last 16: a wave has 32 rows x 16 tokens of each tile (scores in 16 x 16 x 32
+// products, aggregation at K = 16), half the products, operand reads and softmax
+// of a 128-row wave, over a tile that all four waves still dequantize together.
+// Each wave keeps its own reference, sum and accumulators; the two token halves
+// of a row are merged in the epilogue.
+template <int KIND, bool kProt, int kTS>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void decode_kernel(DecodeArgs a) {
+    constexpr int kRowsPerBlock = rows_per_block(kTS);
     // Low-bit kinds take the whole 160 KiB: the staging slots sit at the top,
     // so that the tile slots and the spare bytes below them form one region of
     // at least 128 KiB, which holds the workgroup's query rows in the prologue.
@@ -605,6 +632,8 @@ void decode_kernel(DecodeArgs a) {
     const int lane = tid & 63;
     const int wave = tid >> 6;
     const int half = lane >> 5;
+    const int rw = kTS == 1 ? wave : wave & 1;          // 32-row block of the workgroup's rows
+    const int tw = kTS == 1 ? 0 : wave >> 1;            // token half of each tile (kTS = 2)
     const int rows_total = a.s_q * a.H;
     const int RB = (rows_total + kRowsPerBlock - 1) / kRowsPerBlock;
 
@@ -650,7 +679,7 @@ void decode_kernel(DecodeArgs a) {
     const int32_t* bt = a.block_table + static_cast<int64_t>(b) * a.max_pages;
 
     // this lane's query row
-    const int row = rb * kRowsPerBlock + wave * 32 + (lane & 31);
+    const int row = rb * kRowsPerBlock + rw * 32 + (lane & 31);
     const bool row_ok = row < rows_total;
     const int qi = row_ok ? row / a.H : 0;
     const int h = row_ok ? row % a.H : 0;
@@ -773,7 +802,10 @@ void decode_kernel(DecodeArgs a) {
         // conversion (rows past the end read row 0 of the sequence; they are
         // never stored)
         static_assert(C::D <= 3, "prologue page ids");
-        const int64_t qrow = (static_cast<int64_t>(b) * a.s_q + qi) * a.H + h;
+        // k-step kk of the scores: kTS = 1, channels 16 kk + 8 half .. +8 of row
+        // l % 32 (36 steps); kTS = 2, operand 18 r + kk holds channels 32 kk +
+        // 8 (l / 16) .. +8 of row 16 r + l % 16 (18 steps of two row blocks)
+        const int l16 = lane & 15, g16 = lane >> 4;
         uint4 rawq[kKSteps];
         // The wave's 32 content rows (1 KiB each) are read whole, one
         // direct-to-LDS load per row, into LDS that the prologue's staging
@@ -791,7 +823,7 @@ void decode_kernel(DecodeArgs a) {
                       "query rows fit the free LDS");
         const uint8_t* qseq = reinterpret_cast<const uint8_t*>(a.q_lat) +
                               static_cast<int64_t>(b) * rows_total * (kDc * 2);
-        const int qr0 = rb * kRowsPerBlock + wave_u * 32;
+        const int qr0 = rb * kRowsPerBlock + (kTS == 1 ? wave_u : wave_u & 1) * 32;
         const uint32_t qdst = lds_addr(smem) + kQOff + static_cast<uint32_t>(wave_u * kQRows) * (kDc * 2);
         auto q_round = [&](int r) __attribute__((always_inline)) {
 #pragma unroll
@@ -804,7 +836,17 @@ void decode_kernel(DecodeArgs a) {
         };
         const uint8_t* qrow_lds = smem + kQOff + (wave * kQRows + (lane & 31) % kQRows) * (kDc * 2);
         auto q_read = [&](int r) __attribute__((always_inline)) {
-            if ((lane & 31) / kQRows == r) {
+            if constexpr (kTS == 2) {
+                // row block q of the wave, from the round that staged its rows
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    if (q * 16 / kQRows != r) continue;
+                    const uint8_t* rows = smem + kQOff + (wave * kQRows + (q * 16) % kQRows + l16) * (kDc * 2);
+#pragma unroll
+                    for (int kk = 0; kk < 16; ++kk)
+                        rawq[18 * q + kk] = *reinterpret_cast<const uint4*>(rows + 16 * ((4 * kk + g16) ^ l16));
+                }
+            } else if ((lane & 31) / kQRows == r) {
 #pragma unroll
                 for (int kk = 0; kk < 32; ++kk)
                     rawq[kk] = *reinterpret_cast<const uint4*>(qrow_lds + 16 * ((2 * kk + half) ^ (lane & 15)));
@@ -821,9 +863,21 @@ void decode_kernel(DecodeArgs a) {
             issue_page_ids3(bt, pidx(0), pidx(1), pidx(2), pids[0], pids[1], pids[2]);
         }
         {
-            const uint16_t* qr = a.q_rope + qrow * 64 + 8 * half;
+            if constexpr (kTS == 2) {
 #pragma unroll
-            for (int kk = 32; kk < kKSteps; ++kk) rawq[kk] = *reinterpret_cast<const uint4*>(qr + 16 * (kk - 32));
+                for (int q = 0; q < 2; ++q) {
+                    // rows past the end read row 0 of the sequence
+                    const int rr = qr0 + 16 * q + l16;
+                    const uint16_t* qr = a.q_rope + (static_cast<int64_t>(b) * rows_total + (rr < rows_total ? rr : 0)) * 64 + 8 * g16;
+                    rawq[18 * q + 16] = *reinterpret_cast<const uint4*>(qr);
+                    rawq[18 * q + 17] = *reinterpret_cast<const uint4*>(qr + 32);
+                }
+            } else {
+                const int64_t qrow = (static_cast<int64_t>(b) * a.s_q + qi) * a.H + h;
+                const uint16_t* qr = a.q_rope + qrow * 64 + 8 * half;
+#pragma unroll
+                for (int kk = 32; kk < kKSteps; ++kk) rawq[kk] = *reinterpret_cast<const uint4*>(qr + 16 * (kk - 32));
+            }
         }
         if constexpr (!kRing) wait_page_ids3(pids[0], pids[1], pids[2]);
 #pragma unroll
@@ -846,7 +900,7 @@ void decode_kernel(DecodeArgs a) {
             q_read(1);
         }
 
-        // queries as B operands: k-step kk holds channels 16kk + 8*half .. +8
+        // queries as B operands
         OpT qf[kKSteps];
         {
 #pragma unroll
@@ -867,19 +921,22 @@ void decode_kernel(DecodeArgs a) {
         // per-lane addressing of the transposing V^T reads: lane (group g, index i)
         // supplies the address of tile row k0 + i/4, channels n0 + 4(i%4) .. +3
         // and receives rows k0 .. k0+3 of channel n0 + i
-        const int qk_row = lane & 31;
+        // (kTS = 1: rows 4 (g / 2) + 16 ks, then + 8, the order of the score
+        // registers; kTS = 2: rows 8 (g / 2) of the wave's 16 tokens, then + 4)
+        const int qk_row = kTS == 1 ? lane & 31 : 16 * tw + l16;
         const int tr_i = lane & 15;
         const int tr_g = lane >> 4;
-        const int tr_kbase = 4 * (tr_g >> 1) + (tr_i >> 2);   // + 16 * ks (+ 8 for the second read)
+        const int tr_kbase = kTS == 1 ? 4 * (tr_g >> 1) + (tr_i >> 2) : 16 * tw + 8 * (tr_g >> 1) + (tr_i >> 2);
         const int tr_col = 16 * (tr_g & 1) + 4 * (tr_i & 3);  // + 32 * m
 
-        OpT pb_prev[2] = {OpT{}, OpT{}};   // weights of the previous tile (P^T operands)
+        constexpr int kPB = kTS == 1 ? 2 : 1;      // P^T operands of a wave's tokens (16 each)
+        OpT pb_prev[kPB] = {};             // weights of the previous tile (P^T operands)
         // BF16 pipeline over protected rows: the weights' residuals w - bf16(w),
         // rounded to bf16, as a second P^T operand, so that the aggregation sees
         // each weight to 16 significant bits (bf16 alone keeps 8).  Over the BF16
         // cache one bf16 operand, the normalizer summing the rounded weights.
         constexpr bool kPairW = !C::lowbit && kRing;
-        OpT pl_prev[kPairW ? 2 : 1] = {};
+        OpT pl_prev[kPairW ? kPB : 1] = {};
         int pid_next = 0;                  // page id of the tile the next step stages
         bool move_pending = false;         // the previous tile moved the reference:
         float alpha_pending = 1.0f;        // accumulators *= alpha before its aggregation
@@ -903,7 +960,10 @@ void decode_kernel(DecodeArgs a) {
             const int stage_j = it + C::D;
             constexpr int kStageQ = C::D % (C::lowbit ? C::NS : C::NT);    // slot of tile it + D
 
-            f32x16 s;
+            constexpr int kScores = kTS == 1 ? 16 : 8;     // per lane
+            f32x16 s16;
+            f32x4 s4[2];
+            float s[kScores];
             if constexpr (kQK) {
                 const uint8_t* kt = tiles + tofs[0];
                 // every wave computes, also one whose rows all lie past the end
@@ -923,9 +983,13 @@ void decode_kernel(DecodeArgs a) {
                     dq_read<kDqKind>(dq, stages + sofs[1], tid);
                 }
                 // k-step kk reads logical chunk 2kk + half: physical 2kk + half (+ kk/4 grouped)
-                const uint8_t* krow = kt + row_off(C::SC, qk_row) + 16 * half;
-                auto kread_off = [](int kk) { return 16 * (2 * kk + (C::grouped ? kk >> 2 : 0)); };
+                // (kTS = 2: chunk 4kk + g16, physical + kk/2)
+                const uint8_t* krow = kt + row_off(C::SC, qk_row) + 16 * (kTS == 1 ? half : g16);
+                auto kread_off = [](int kk) {
+                    return kTS == 1 ? 16 * (2 * kk + (C::grouped ? kk >> 2 : 0)) : 16 * (4 * kk + (C::grouped ? kk >> 1 : 0));
+                };
                 constexpr int kAhead = 4;
+                constexpr int kReads = kKSteps / kTS;
                 OpT kb[kAhead];
 #pragma unroll
                 for (int j = 0; j < kAhead; ++j) kb[j] = *reinterpret_cast<const OpT*>(krow + kread_off(j));
@@ -935,20 +999,47 @@ void decode_kernel(DecodeArgs a) {
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int kk = 0; kk < kKSteps; ++kk) {
-                    const int ko = kk ^ 1;          // 2p+1 first, then 2p
-                    mfma_v(s, kb[ko % kAhead], qf[ko], kk == 0);
-                    if (kk & 1) {
+                    if constexpr (kTS == 1) {
+                        const int ko = kk ^ 1;          // 2p+1 first, then 2p
+                        mfma_v(s16, kb[ko % kAhead], qf[ko], kk == 0);
+                        if (kk & 1) {
 #pragma unroll
-                        for (int j = kk - 1; j <= kk; ++j)
-                            if (j + kAhead < kKSteps) kb[j % kAhead] = *reinterpret_cast<const OpT*>(krow + kread_off(j + kAhead));
+                            for (int j = kk - 1; j <= kk; ++j)
+                                if (j + kAhead < kReads) kb[j % kAhead] = *reinterpret_cast<const OpT*>(krow + kread_off(j + kAhead));
+                        }
+                    } else {
+                        // operand kk / 2 with both row blocks, pairs of operands in reverse
+                        // order as above
+                        const int ko = (kk >> 1) ^ 1;
+                        mfma_v(s4[kk & 1], kb[ko % kAhead], qf[18 * (kk & 1) + ko], kk < 2);
+                        if ((kk & 3) == 3) {
+#pragma unroll
+                            for (int j = ko; j <= ko + 1; ++j)
+                                if (j + kAhead < kReads) kb[j % kAhead] = *reinterpret_cast<const OpT*>(krow + kread_off(j + kAhead));
+                        }
                     }
                     if constexpr (C::lowbit) dq_step<kDqKind>(dq, kk, next_tile, tid);
                     __builtin_amdgcn_sched_barrier(0);
                 }
-                score_ready(s);
+                if constexpr (kTS == 1) {
+                    score_ready(s16);
+#pragma unroll
+                    for (int v = 0; v < kScores; ++v) s[v] = s16[v];
+                } else {
+                    // the lanes of the two row blocks exchange, so that lane l holds row
+                    // l % 32, tokens 16 tw + 8 half + v
+                    score_ready(s4[0], s4[1]);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(s4[0][v]), __float_as_uint(s4[1][v]),
+                                                                        false, false);
+                        s[v] = __uint_as_float(x[0]);
+                        s[(4 + v) % kScores] = __uint_as_float(x[1]);
+                    }
+                }
                 if constexpr (C::lowbit) {
 #pragma unroll
-                    for (int s = kKSteps; s < kDqSteps; ++s) dq_step<kDqKind>(dq, s, next_tile, tid);
+                    for (int q = kKSteps; q < kDqSteps; ++q) dq_step<kDqKind>(dq, q, next_tile, tid);
                 }
                 // rows see every key of the tile except in the last tile of the
                 // range or the tile holding the newest key (block-uniform test)
@@ -959,8 +1050,8 @@ void decode_kernel(DecodeArgs a) {
                 if constexpr (kProt) edge = edge || t0 < t_lo;
                 if (edge) {
 #pragma unroll
-                    for (int v = 0; v < 16; ++v) {
-                        const int t = t0 + 8 * (v >> 2) + 4 * half + (v & 3);
+                    for (int v = 0; v < kScores; ++v) {
+                        const int t = t0 + (kTS == 1 ? 8 * (v >> 2) + 4 * half + (v & 3) : 16 * tw + 8 * half + v);
                         bool ok = t < lim;
                         if constexpr (kProt) ok = ok && t >= t_lo;
                         s[v] = ok ? s[v] : -INFINITY;
@@ -978,14 +1069,16 @@ void decode_kernel(DecodeArgs a) {
 
             // Softmax of tile it in pieces (interleaved with the aggregation of
             // tile it-1 when there is one, a piece every second product, the
-            // staging loads after them): 0-1 the tile maximum, 2 the reference
-            // (a move reaches the accumulators in the next step), 3-10 the
+            // staging loads after them): the tile maximum (8 scores per piece), the
+            // reference (a move reaches the accumulators in the next step), the
             // weights, two per piece.
             float mr = -INFINITY, nref = 0.0f;
             bool move = false;
             float alpha = 1.0f;
-            uint32_t pw[8];
-            uint32_t pwl[kPairW ? 8 : 1];
+            constexpr int kPw = kScores / 2;
+            constexpr int kMaxPieces = kScores / 8, kPieces = kMaxPieces + 1 + kPw;
+            uint32_t pw[kPw];
+            uint32_t pwl[kPairW ? kPw : 1];
             // (The empty statements pin each piece's results where it is computed:
             // the compiler would otherwise sink the work next to its first use,
             // after the aggregation.)
@@ -994,13 +1087,14 @@ void decode_kernel(DecodeArgs a) {
                     mr = s[0];
 #pragma unroll
                     for (int v = 1; v < 8; ++v) mr = fmaxf(mr, s[v]);
+                    if constexpr (kMaxPieces == 1) mr = max_halves(mr);
                     asm volatile("" : "+v"(mr));
-                } else if (q == 1) {
+                } else if (q < kMaxPieces) {
 #pragma unroll
-                    for (int v = 8; v < 16; ++v) mr = fmaxf(mr, s[v]);
+                    for (int v = 8; v < kScores; ++v) mr = fmaxf(mr, s[v]);
                     mr = max_halves(mr);
                     asm volatile("" : "+v"(mr));
-                } else if (q == 2) {
+                } else if (q == kMaxPieces) {
                     const float mt = mr * a.scale_log2;           // scale > 0: max commutes
                     m_true = fmaxf(m_true, mt);
                     if (m_ref == -INFINITY) m_ref = mt;          // first visible key: nothing accumulated yet
@@ -1011,8 +1105,8 @@ void decode_kernel(DecodeArgs a) {
                     l_run *= alpha;
                     nref = m_ref == -INFINITY ? 0.0f : -m_ref;
                     asm volatile("" : "+v"(nref), "+v"(l_run), "+v"(m_ref), "+v"(m_true), "+v"(alpha));
-                } else if (q < 11) {
-                    const int v2 = q - 3;
+                } else if (q < kPieces) {
+                    const int v2 = q - kMaxPieces - 1;
                     const float p0 = __builtin_amdgcn_exp2f(fmaf(s[2 * v2], a.scale_log2, nref));
                     const float p1 = __builtin_amdgcn_exp2f(fmaf(s[2 * v2 + 1], a.scale_log2, nref));
                     if constexpr (C::lowbit) {
@@ -1026,8 +1120,8 @@ void decode_kernel(DecodeArgs a) {
                         // w - bf16(w) is exact in fp32 (|r| <= 2^-9 |w|); its bf16 rounding
                         // leaves each weight to a relative 2^-17
                         const float h0 = __uint_as_float(pw[v2] << 16), h1 = __uint_as_float(pw[v2] & 0xFFFF0000u);
-                        pwl[v2 % (kPairW ? 8 : 1)] = pack_bf16x2(p0 - h0, p1 - h1);
-                        asm volatile("" : "+v"(pwl[v2 % (kPairW ? 8 : 1)]));
+                        pwl[v2 % (kPairW ? kPw : 1)] = pack_bf16x2(p0 - h0, p1 - h1);
+                        asm volatile("" : "+v"(pwl[v2 % (kPairW ? kPw : 1)]));
                     } else {
                         // the sum of the bf16 weights the aggregation uses, one dot2 per pair
                         typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -1039,7 +1133,10 @@ void decode_kernel(DecodeArgs a) {
                     asm volatile("" : "+v"(pw[v2]), "+v"(l_run));
                 }
             };
-            constexpr int kStageSlot0 = C::lowbit ? 23 : 13, kStageGap = C::lowbit ? 3 : 2;
+            constexpr int kStageSlot0 = kTS == 1 ? (C::lowbit ? 23 : 13) : (C::lowbit ? 9 : 5);
+            constexpr int kStageGap = kTS == 1 ? (C::lowbit ? 3 : 2) : (C::lowbit ? 2 : 1);
+            constexpr int kProducts = 32 / kTS;
+            static_assert(kStageSlot0 + (C::loads - 1) * kStageGap < kProducts && 2 * (kPieces - 1) < kProducts, "pieces fit the products");
 
             if constexpr (kPV) {
                 // latent aggregation of tile it-1: O^T[channel][row] += V^T . P^T;
@@ -1049,12 +1146,13 @@ void decode_kernel(DecodeArgs a) {
                 // channels 32 m + tr_col ..: logical chunk 4m + (0..3), physical
                 // + m/2 in the grouped layout
                 const uint8_t* vt = tiles + tofs[C::NT - 1];
+                constexpr int kSecond = kTS == 1 ? 16 * C::SC * 8 + 32 : 16 * C::SC * 4 + 16;   // row_off of 8 (4) rows on
                 const uint8_t* vbase = vt + row_off(C::SC, tr_kbase) + 2 * tr_col;
                 auto vread = [&](int stp) __attribute__((always_inline)) {
                     const int ks = stp >> 4, m = stp & 15;
                     const uint8_t* p = vbase + 16 * C::SC * 16 * ks + 64 * m + (C::grouped ? 16 * (m >> 1) : 0);
                     const i16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)p);
-                    const i16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(p + 16 * C::SC * 8 + 32));
+                    const i16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(p + kSecond));
                     return __builtin_bit_cast(OpT, __builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7));
                 };
                 // operands read in pairs one pair ahead; the pair (2p, 2p+1) is
@@ -1065,15 +1163,15 @@ void decode_kernel(DecodeArgs a) {
                 for (int j = 0; j < kVAhead; ++j) vb[j] = vread(j);
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int stp = 0; stp < 32; ++stp) {
+                for (int stp = 0; stp < kProducts; ++stp) {
                     const int so = stp ^ 1;
                     const int m = so & 15;
                     acc[m] = mfma(vb[so % kVAhead], pb_prev[so >> 4], acc[m]);
-                    if constexpr (kPairW) acc[m] = mfma(vb[so % kVAhead], pl_prev[(so >> 4) % 2], acc[m]);
+                    if constexpr (kPairW) acc[m] = mfma(vb[so % kVAhead], pl_prev[(so >> 4) % kPB], acc[m]);
                     if (stp & 1) {
 #pragma unroll
                         for (int j = stp - 1; j <= stp; ++j)
-                            if (j + kVAhead < 32) vb[j % kVAhead] = vread(j + kVAhead);
+                            if (j + kVAhead < kProducts) vb[j % kVAhead] = vread(j + kVAhead);
                     }
                     if constexpr (kQK) {
                         if (stp % 2 == 0) softmax_piece(stp / 2);
@@ -1086,18 +1184,16 @@ void decode_kernel(DecodeArgs a) {
                 }
             } else if constexpr (kQK) {
 #pragma unroll
-                for (int q = 0; q < 11; ++q) softmax_piece(q);
+                for (int q = 0; q < kPieces; ++q) softmax_piece(q);
 #pragma unroll
                 for (int k = 0; k < C::loads; ++k) issue(k, pid, cur_t0, cur_po, stage_slot(kStageQ));
             }
             if constexpr (kQK) {
-                pb_prev[0] = __builtin_bit_cast(OpT, make_uint4(pw[0], pw[1], pw[2], pw[3]));
-                pb_prev[1] = __builtin_bit_cast(OpT, make_uint4(pw[4], pw[5], pw[6], pw[7]));
-                if constexpr (kPairW) {
-                    constexpr int n = kPairW ? 8 : 1;
-                    pl_prev[0] = __builtin_bit_cast(OpT, make_uint4(pwl[0 % n], pwl[1 % n], pwl[2 % n], pwl[3 % n]));
-                    pl_prev[1 % (kPairW ? 2 : 1)] =
-                        __builtin_bit_cast(OpT, make_uint4(pwl[4 % n], pwl[5 % n], pwl[6 % n], pwl[7 % n]));
+#pragma unroll
+                for (int q = 0; q < kPB; ++q) {
+                    pb_prev[q] = __builtin_bit_cast(OpT, make_uint4(pw[4 * q], pw[4 * q + 1], pw[4 * q + 2], pw[4 * q + 3]));
+                    if constexpr (kPairW)
+                        pl_prev[q] = __builtin_bit_cast(OpT, make_uint4(pwl[4 * q], pwl[4 * q + 1], pwl[4 * q + 2], pwl[4 * q + 3]));
                 }
                 move_pending = move;
                 alpha_pending = alpha;
@@ -1203,10 +1299,77 @@ void decode_kernel(DecodeArgs a) {
     // of 16-byte pieces of 32 rows: wave w stages its 32 rows at 1040-byte
     // pitch (the 16-byte shift per row spreads the 32 rows of a write over the
     // banks), then reads them back row by row.
-    const float l_tot = sum_halves(l_run);
+    float l_tot = sum_halves(l_run);
     const bool split_out = a.split_tokens != 0;
     const float inv = l_tot > 0.0f ? 1.0f / l_tot : 0.0f;
     __syncthreads();        // every wave is done with the tiles (no staging load is in flight)
+    const int row0 = rb * kRowsPerBlock + rw * 32;      // the wave's rows of the output, or of work item w's partials
+    uint16_t* dst = split_out ? a.part_o + (static_cast<int64_t>(w) * rows_total + row0) * kDc
+                              : a.out + (static_cast<int64_t>(b) * rows_total + row0) * kDc;
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    auto pack4 = [&](float x0, float x1, float x2, float x3) {
+        // partials: the split's normalized aggregation in fp16 (the combine
+        // weighs it by part_s); unsplit: the output in bf16
+        return split_out ? make_uint2(pack_f16x2(x0, x1), pack_f16x2(x2, x3))
+                         : make_uint2(pack_bf16x2(x0, x1), pack_bf16x2(x2, x3));
+    };
+    if constexpr (kTS == 2) {
+        // Merge of the two token halves: one reference for the row's two parts
+        // (a part with no visible key has m_ref = -inf and weighs 0), the fp32
+        // accumulators through LDS, 256 channels at a time; of a pair of waves
+        // each sums and stores 16 of the 32 rows.
+        constexpr int kPitch = 1040;
+        constexpr int kRegion = 32 * kPitch;
+        static_assert(kWaves * kRegion + 3 * kWaves * 32 * 4 <= kLds, "merged rows fit the LDS");
+        float* sh = reinterpret_cast<float*>(smem + kWaves * kRegion);      // [3][wave][32]
+        if (half == 0) {
+            sh[wave * 32 + lane] = m_ref;
+            sh[(kWaves + wave) * 32 + lane] = l_tot;
+            sh[(2 * kWaves + wave) * 32 + lane] = m_true;
+        }
+        __syncthreads();
+        const int other = (wave ^ 2) * 32 + (lane & 31);
+        const float own = m_ref, m2 = sh[other], l2 = sh[kWaves * 32 + other];
+        m_ref = fmaxf(own, m2);
+        m_true = fmaxf(m_true, sh[2 * kWaves * 32 + other]);
+        const float nref = m_ref == -INFINITY ? 0.0f : m_ref;
+        const float f1 = __builtin_amdgcn_exp2f(own - nref), f2 = __builtin_amdgcn_exp2f(m2 - nref);
+        l_tot = tw == 0 ? f1 * l_tot + f2 * l2 : f2 * l2 + f1 * l_tot;
+        const float f = (l_tot > 0.0f ? 1.0f / l_tot : 0.0f) * f1;
+        uint8_t* ep = smem + wave * kRegion;
+#pragma unroll
+        for (int rd = 0; rd < 2; ++rd) {
+            if (rd > 0) __syncthreads();
+#pragma unroll
+            for (int m = 0; m < 8; ++m)
+#pragma unroll
+                for (int q4 = 0; q4 < 4; ++q4) {
+                    const f32x16& x = acc[8 * rd + m];
+                    *reinterpret_cast<float4*>(ep + (lane & 31) * kPitch + 4 * (32 * m + 8 * q4 + 4 * half)) =
+                        make_float4(x[4 * q4] * f, x[4 * q4 + 1] * f, x[4 * q4 + 2] * f, x[4 * q4 + 3] * f);
+                }
+            __syncthreads();
+            // (rows past the end repeat the last one, as below)
+            const int last = rows_total - 1 - row0;
+            if (last >= 0) {
+#pragma unroll
+                for (int i0 = 0; i0 < 16; i0 += 8) {
+                    float4 x[8], y[8];
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        const int r = min(16 * tw + i0 + i, last);
+                        x[i] = *reinterpret_cast<const float4*>(smem + rw * kRegion + r * kPitch + 16 * lane);
+                        y[i] = *reinterpret_cast<const float4*>(smem + (rw + 2) * kRegion + r * kPitch + 16 * lane);
+                    }
+#pragma unroll
+                    for (int i = 0; i < 8; ++i)
+                        *reinterpret_cast<uint2*>(dst + min(16 * tw + i0 + i, last) * kDc + 256 * rd + 4 * lane) =
+                            pack4(x[i].x + y[i].x, x[i].y + y[i].y, x[i].z + y[i].z, x[i].w + y[i].w);
+                }
+            }
+        }
+        if (tw != 0) return;
+    } else {
     constexpr int kRowPitch = 1040;
     static_assert(kWaves * 32 * kRowPitch <= kLds, "epilogue rows fit the LDS");
     uint8_t* ep = smem + wave * 32 * kRowPitch;
@@ -1216,27 +1379,28 @@ void decode_kernel(DecodeArgs a) {
         for (int q4 = 0; q4 < 4; ++q4) {
             const float x0 = acc[m][4 * q4] * inv, x1 = acc[m][4 * q4 + 1] * inv;
             const float x2 = acc[m][4 * q4 + 2] * inv, x3 = acc[m][4 * q4 + 3] * inv;
-            // partials: the split's normalized aggregation in fp16 (the combine
-            // weighs it by part_s); unsplit: the output in bf16
-            const uint2 u = split_out ? make_uint2(pack_f16x2(x0, x1), pack_f16x2(x2, x3))
-                                      : make_uint2(pack_bf16x2(x0, x1), pack_bf16x2(x2, x3));
-            *reinterpret_cast<uint2*>(ep + (lane & 31) * kRowPitch + 2 * (32 * m + 8 * q4 + 4 * half)) = u;
+            *reinterpret_cast<uint2*>(ep + (lane & 31) * kRowPitch + 2 * (32 * m + 8 * q4 + 4 * half)) = pack4(x0, x1, x2, x3);
         }
     }
-    // rows r = row block + 32 wave + i are (b, i, h) rows of the output, or of
-    // work item w's partials
-    const int row0 = rb * kRowsPerBlock + wave * 32;
-    uint16_t* dst = split_out ? a.part_o + (static_cast<int64_t>(w) * rows_total + row0) * kDc
-                              : a.out + (static_cast<int64_t>(b) * rows_total + row0) * kDc;
     // Non-temporal stores: every workgroup writes its rows at about the same
     // time, at the end of the launch, and the write burst is the epilogue's
     // bound; written as streaming data they cost less.
-    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    // Rows past the end repeat the wave's last one (the same bytes to the same
+    // place): a test per row would leave every row's LDS read waiting alone
+    // before its store, instead of eight in flight.
+    const int last = rows_total - 1 - row0;
+    if (last >= 0) {
 #pragma unroll
-    for (int i = 0; i < 32; ++i) {
-        if (row0 + i < rows_total)
-            __builtin_nontemporal_store(*reinterpret_cast<const u32x4*>(ep + i * kRowPitch + 16 * lane),
-                                        reinterpret_cast<u32x4*>(dst + i * kDc + 8 * lane));
+        for (int i0 = 0; i0 < 32; i0 += 8) {
+            u32x4 v[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                v[i] = *reinterpret_cast<const u32x4*>(ep + min(i0 + i, last) * kRowPitch + 16 * lane);
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                __builtin_nontemporal_store(v[i], reinterpret_cast<u32x4*>(dst + min(i0 + i, last) * kDc + 8 * lane));
+        }
+    }
     }
     if (!row_ok || half != 0) return;
     if (!split_out) {
@@ -1254,17 +1418,32 @@ void decode_kernel(DecodeArgs a) {
 
 }  // namespace
 
+namespace {
+
+// Up to 64 rows, 64-row workgroups with token-split waves: in a 128-row one half
+// the waves would work on rows that do not exist.  Measured at 64 rows, INT2,
+// per 32-token tile: 1.0-1.3 us against 1.6; 256 work items of 480, 960 and 1 920
+// tokens: 39.7, 56.1, 94.4 us against 42.8, 67.4, 114.1.
+template <int KIND, bool kProt>
+void launch_kind(const DecodeArgs& a, hipStream_t stream, const LaunchEvents& ev) {
+    const int64_t rows = static_cast<int64_t>(a.s_q) * a.H;
+    const int64_t blocks = decode_workgroups(a.num_work, rows, kDecodeRowsPerBlock);
+    const dim3 grid(static_cast<unsigned>(blocks)), block(kThreads);
+    if (rows <= rows_per_block(2)) dispatch_decode(decode_kernel<KIND, kProt, 2>, grid, block, stream, ev, a);
+    else dispatch_decode(decode_kernel<KIND, kProt, 1>, grid, block, stream, ev, a);
+}
+
+}  // namespace
+
 hipError_t launch_decode(CacheKind kind, const DecodeArgs& a, hipStream_t stream) {
     if (a.num_work == 0) return hipSuccess;
     const LaunchEvents ev = take_launch_events();
-    const int64_t blocks = decode_workgroups(a.num_work, static_cast<int64_t>(a.s_q) * a.H, kRowsPerBlock);
-    const dim3 grid(static_cast<unsigned>(blocks)), block(kThreads);
     switch (kind) {
-        case KIND_C4R4: dispatch_decode(decode_kernel<KIND_C4R4, false>, grid, block, stream, ev, a); break;
-        case KIND_C2R4: dispatch_decode(decode_kernel<KIND_C2R4, false>, grid, block, stream, ev, a); break;
-        case KIND_C4R4P: dispatch_decode(decode_kernel<KIND_C4R4P, false>, grid, block, stream, ev, a); break;
-        case KIND_C2R4P: dispatch_decode(decode_kernel<KIND_C2R4P, false>, grid, block, stream, ev, a); break;
-        case KIND_BF16: dispatch_decode(decode_kernel<KIND_BF16, false>, grid, block, stream, ev, a); break;
+        case KIND_C4R4: launch_kind<KIND_C4R4, false>(a, stream, ev); break;
+        case KIND_C2R4: launch_kind<KIND_C2R4, false>(a, stream, ev); break;
+        case KIND_C4R4P: launch_kind<KIND_C4R4P, false>(a, stream, ev); break;
+        case KIND_C2R4P: launch_kind<KIND_C2R4P, false>(a, stream, ev); break;
+        case KIND_BF16: launch_kind<KIND_BF16, false>(a, stream, ev); break;
     }
     return hipGetLastError();
 }
@@ -1272,13 +1451,11 @@ hipError_t launch_decode(CacheKind kind, const DecodeArgs& a, hipStream_t stream
 hipError_t launch_decode_protected(CacheKind kind, const DecodeArgs& a, hipStream_t stream) {
     if (a.num_work == 0) return hipSuccess;
     const LaunchEvents ev = take_launch_events();
-    const int64_t blocks = decode_workgroups(a.num_work, static_cast<int64_t>(a.s_q) * a.H, kRowsPerBlock);
-    const dim3 grid(static_cast<unsigned>(blocks)), block(kThreads);
     switch (kind) {
-        case KIND_C4R4: dispatch_decode(decode_kernel<KIND_C4R4, true>, grid, block, stream, ev, a); break;
-        case KIND_C2R4: dispatch_decode(decode_kernel<KIND_C2R4, true>, grid, block, stream, ev, a); break;
-        case KIND_C4R4P: dispatch_decode(decode_kernel<KIND_C4R4P, true>, grid, block, stream, ev, a); break;
-        case KIND_C2R4P: dispatch_decode(decode_kernel<KIND_C2R4P, true>, grid, block, stream, ev, a); break;
+        case KIND_C4R4: launch_kind<KIND_C4R4, true>(a, stream, ev); break;
+        case KIND_C2R4: launch_kind<KIND_C2R4, true>(a, stream, ev); break;
+        case KIND_C4R4P: launch_kind<KIND_C4R4P, true>(a, stream, ev); break;
+        case KIND_C2R4P: launch_kind<KIND_C2R4P, true>(a, stream, ev); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
