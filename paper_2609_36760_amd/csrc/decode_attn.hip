@@ -516,8 +516,9 @@ __device__ __forceinline__ void append_in_launch(const DecodeArgs& a, int b, int
         const int64_t slot = a.new_slots[tok];
         const int64_t num_slots = a.num_pages * a.g.page_size;
         if (slot >= 0 && slot < num_slots) {
-            uint8_t* base = const_cast<uint8_t*>(a.cache) + slot / a.g.page_size * a.g.page_bytes;
-            const int64_t off = slot % a.g.page_size;
+            const wc::SlotPos at = wc::split_slot(slot, num_slots, a.g);
+            uint8_t* base = const_cast<uint8_t*>(a.cache) + at.page * a.g.page_bytes;
+            const int64_t off = at.off;
             const bool rope = r >= 64;
             const uint16_t* src = rope ? a.new_k + tok * a.new_k_stride + (r - 64) * 8
                                        : a.new_c + tok * a.new_c_stride + r * 8;
@@ -570,8 +571,9 @@ __device__ __forceinline__ void append_in_launch_protected(const DecodeArgs& a, 
         const int64_t slot = a.new_slots[tok];
         const int64_t num_slots = a.num_pages * a.g.page_size;
         if (slot >= 0 && slot < num_slots) {
-            uint8_t* base = const_cast<uint8_t*>(a.cache) + slot / a.g.page_size * a.g.page_bytes;
-            const int64_t off = slot % a.g.page_size;
+            const wc::SlotPos at = wc::split_slot(slot, num_slots, a.g);
+            uint8_t* base = const_cast<uint8_t*>(a.cache) + at.page * a.g.page_bytes;
+            const int64_t off = at.off;
             const bool rope = r >= 64;
             const uint16_t* src = rope ? a.new_k + tok * a.new_k_stride + (r - 64) * 8
                                        : a.new_c + tok * a.new_c_stride + r * 8;

@@ -268,8 +268,9 @@ __device__ __forceinline__ void narrow_append(const DecodeArgs& a, int b, int L,
         const int64_t tok = static_cast<int64_t>(b) * a.s_q + i;
         const int64_t slot = a.new_slots[tok];
         if (slot < 0 || slot >= num_slots) continue;
-        uint8_t* base = const_cast<uint8_t*>(a.cache) + slot / a.g.page_size * a.g.page_bytes;
-        const int64_t off = slot % a.g.page_size;
+        const wc::SlotPos at = wc::split_slot(slot, num_slots, a.g);
+        uint8_t* base = const_cast<uint8_t*>(a.cache) + at.page * a.g.page_bytes;
+        const int64_t off = at.off;
         const bool rope = r >= 64;
         const uint16_t* src = rope ? a.new_k + tok * a.new_k_stride + (r - 64) * 8
                                    : a.new_c + tok * a.new_c_stride + r * 8;
@@ -1147,9 +1148,12 @@ void launch_rows(const DecodeArgs& a, hipStream_t stream, const LaunchEvents& ev
 
 // One 32-row wave for 17 to 32 rows: each tile is dequantized once, where two
 // 16-row waves would do it twice (1.4 us per 16 tokens, against twice 1.5).
+// While two 16-row workgroups per work item still leave every workgroup a unit
+// of its own, those are shorter (fixed costs of about 9 us against 13).
 template <int KIND, bool kProt>
 void launch_kind(const DecodeArgs& a, hipStream_t stream, const LaunchEvents& ev) {
-    if (a.s_q * a.H <= 16) launch_rows<KIND, kProt, 16>(a, stream, ev);
+    const int rows = a.s_q * a.H;
+    if (rows <= 16 || decode_workgroups(a.num_work, rows, 16) <= kCus) launch_rows<KIND, kProt, 16>(a, stream, ev);
     else launch_rows<KIND, kProt, kMaxRows>(a, stream, ev);
 }
 

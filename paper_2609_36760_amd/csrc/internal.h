@@ -19,6 +19,7 @@ struct PageGeom {
     int32_t off_mr;         // (fp16 metadata only)
     int64_t page_bytes;
     int32_t paper_meta;     // 1: the paper's metadata record at off_mc
+    uint32_t page_magic;    // floor(2^32 / page_size): split_slot in writer_common.h
 };
 
 struct AppendArgs {

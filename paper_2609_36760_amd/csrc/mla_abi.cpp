@@ -78,10 +78,16 @@ int check_lowbit_format(const mla_cache_format* f) {
     return MLA_OK;
 }
 
+// page_size >= 32, so the quotient fits 32 bits
+uint32_t page_magic(int32_t page_size) {
+    return static_cast<uint32_t>((uint64_t{1} << 32) / static_cast<uint32_t>(page_size));
+}
+
 mla::PageGeom lowbit_geom(const mla_cache_format* f) {
     mla::PageGeom g{};
     const int32_t P = f->page_size;
     g.page_size = P;
+    g.page_magic = page_magic(P);
     g.c_bits = f->c_bits;
     g.cc_bytes = f->d_c * f->c_bits / 8;
     g.cr_bytes = f->d_r * f->r_bits / 8;
@@ -104,6 +110,7 @@ mla::PageGeom lowbit_geom(const mla_cache_format* f) {
 mla::PageGeom bf16_geom(const mla_cache_format* f) {
     mla::PageGeom g{};
     g.page_size = f->page_size;
+    g.page_magic = page_magic(f->page_size);
     g.page_bytes = static_cast<int64_t>(f->page_size) * (f->d_c + f->d_r) * 2;
     return g;
 }

@@ -25,38 +25,46 @@ static_assert(kGroupsPerToken * kLanesPerGroup == kAppendThreadsPerToken, "launc
 
 template <int CBITS, bool kProt, bool kPaper>
 __global__ __launch_bounds__(kThreads) void lowbit_append_kernel(AppendArgs a) {
-    const int64_t tid = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
-    const int64_t gid = tid / kLanesPerGroup;           // the 8 lanes of a group share gid
+    // the launch's work items fit 32 bits (the host refuses more tokens)
+    const uint32_t gid = (blockIdx.x * kThreads + threadIdx.x) / kLanesPerGroup;    // shared by a group's 8 lanes
     const int lig = static_cast<int>(threadIdx.x % kLanesPerGroup);
-    if (gid >= static_cast<int64_t>(a.n) * kGroupsPerToken) return;
-    const int64_t token = gid / kGroupsPerToken;
-    const int g = static_cast<int>(gid % kGroupsPerToken);
-    const int64_t slot = a.slot_mapping[token];
-    if (slot < 0 || slot >= a.num_slots) return;        // skipped token
-
+    const uint32_t tok32 = gid / kGroupsPerToken;
+    if (tok32 >= static_cast<uint32_t>(a.n)) return;
+    const int64_t token = tok32;
+    const int g = static_cast<int>(gid - tok32 * kGroupsPerToken);
+    // Everything that depends on the token alone is loaded before anything is
+    // tested (a skipped token's row is read for nothing), so that the memory round
+    // trips overlap: one for the row, its slot, sequence and position, and under
+    // protection a second one for the sequence's length and buffer.
     const bool rope = (g == kGroupsPerToken - 1);
     const uint16_t* src = rope ? a.k_rope + token * a.k_rope_stride + lig * 8
                                : a.c_kv + token * a.c_kv_stride + g * kGroup + lig * 8;
     const uint4 raw = *reinterpret_cast<const uint4*>(src);
+    const int64_t slot = a.slot_mapping[token];
+    int bseq = -1, p = 0, L = 0;
+    int64_t ps = -1;
+    if constexpr (kProt) {
+        bseq = a.token_seq[token];
+        p = a.positions[token];
+        const int bs = min(max(bseq, 0), a.B - 1);      // B >= 1
+        L = a.seq_lens[bs];
+        ps = a.prot_slot[bs];
+    }
+    if (slot < 0 || slot >= a.num_slots) return;        // skipped token
 
     if constexpr (kProt) {
-        const int bseq = a.token_seq[token];
-        if (bseq >= 0 && bseq < a.B) {
-            const int p = a.positions[token];
-            const int L = a.seq_lens[bseq];
-            const int64_t ps = a.prot_slot[bseq];
-            // p >= L - recent with p < L implies recent >= 1
-            if (p >= 0 && p < L && (p < a.sink || p >= L - a.recent) && ps >= 0 && ps < a.num_prot) {
-                const int prow = p < a.sink ? p : a.sink + (p - a.sink) % a.recent;
-                uint8_t* dst = a.prot + (ps * (a.sink + a.recent) + prow) * 1152 +
-                               (rope ? 1024 + lig * 16 : (g * kGroup + lig * 8) * 2);
-                *reinterpret_cast<uint4*>(dst) = raw;
-            }
+        // p >= L - recent with p < L implies recent >= 1
+        if (bseq >= 0 && bseq < a.B && p >= 0 && p < L && (p < a.sink || p >= L - a.recent) && ps >= 0 &&
+            ps < a.num_prot) {
+            const int prow = p < a.sink ? p : a.sink + (p - a.sink) % a.recent;
+            uint8_t* dst = a.prot + (ps * (a.sink + a.recent) + prow) * 1152 +
+                           (rope ? 1024 + lig * 16 : (g * kGroup + lig * 8) * 2);
+            *reinterpret_cast<uint4*>(dst) = raw;
         }
     }
 
-    wc::quantize_store<CBITS, kPaper>(raw, rope, g, lig, a.cache + slot / a.g.page_size * a.g.page_bytes,
-                                      slot % a.g.page_size, a.g);
+    const wc::SlotPos at = wc::split_slot(slot, a.num_slots, a.g);
+    wc::quantize_store<CBITS, kPaper>(raw, rope, g, lig, a.cache + at.page * a.g.page_bytes, at.off, a.g);
 }
 
 // BF16 comparison cache: row = [c_kv (512) | k_rope (64)] bf16; 72 lanes per
@@ -64,17 +72,17 @@ __global__ __launch_bounds__(kThreads) void lowbit_append_kernel(AppendArgs a) {
 __global__ __launch_bounds__(kThreads) void bf16_append_kernel(AppendArgs a) {
     constexpr int kLanesPerToken = 72;     // 64 content + 8 RoPE pieces of 16 bytes
     static_assert(kLanesPerToken == kAppendThreadsPerToken, "launch shape the host checks");
-    const int64_t tid = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
-    const int64_t token = tid / kLanesPerToken;
-    const int lane = static_cast<int>(tid % kLanesPerToken);
-    if (token >= a.n) return;
+    const uint32_t tid = blockIdx.x * kThreads + threadIdx.x;      // fits 32 bits, as above
+    const uint32_t tok32 = tid / kLanesPerToken;
+    const int lane = static_cast<int>(tid - tok32 * kLanesPerToken);
+    if (tok32 >= static_cast<uint32_t>(a.n)) return;
+    const int64_t token = tok32;
     const int64_t slot = a.slot_mapping[token];
     if (slot < 0 || slot >= a.num_slots) return;
     const uint16_t* src = lane < 64 ? a.c_kv + token * a.c_kv_stride + lane * 8
                                     : a.k_rope + token * a.k_rope_stride + (lane - 64) * 8;
-    const int64_t page = slot / a.g.page_size;
-    const int64_t off = slot % a.g.page_size;
-    uint8_t* dst = a.cache + page * a.g.page_bytes + off * 1152 + lane * 16;
+    const wc::SlotPos at = wc::split_slot(slot, a.num_slots, a.g);
+    uint8_t* dst = a.cache + at.page * a.g.page_bytes + at.off * 1152 + lane * 16;
     *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>(src);
 }
 

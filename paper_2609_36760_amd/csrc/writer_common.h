@@ -10,7 +10,9 @@
 // scale and zero are what attention dequantizes with.  Every step is one IEEE
 // fp32 operation in that order (explicitly rounded subtractions and divisions;
 // no step multiplies, so no contraction can merge two), so the codes and fp16
-// metadata are bit-identical to any IEEE implementation of the formula.
+// metadata are bit-identical to any IEEE implementation of the formula.  The
+// quotients by s come from its reciprocal where that is proven to give the
+// same bits (fast_div below).
 //
 // Metadata: fp16(s) and fp16(z) per group (MLA_META_FP16); or the paper's
 // storage (Appendix C.4, last sentence): bf16(s) (round-half-to-even) for the
@@ -51,6 +53,46 @@ __device__ __forceinline__ uint16_t f16_bits(float v) {
     return __builtin_bit_cast(uint16_t, h);
 }
 
+// Page and offset of a slot below num_slots.  Up to 2^32 slots in 32 bits:
+// umulhi(n, floor(2^32 / P)) falls short of n / P by less than n / 2^32 < 1, so
+// its floor is the quotient or one less (a 64-bit division by a run-time
+// divisor takes about 100 instructions).
+struct SlotPos {
+    int64_t page, off;
+};
+__device__ __forceinline__ SlotPos split_slot(int64_t slot, int64_t num_slots, const PageGeom& g) {
+    if (num_slots <= (int64_t{1} << 32)) {
+        const uint32_t n = static_cast<uint32_t>(slot), P = static_cast<uint32_t>(g.page_size);
+        uint32_t q = __umulhi(n, g.page_magic), r = n - q * P;
+        if (r >= P) {
+            ++q;
+            r -= P;
+        }
+        return {q, r};
+    }
+    return {slot / g.page_size, slot % g.page_size};
+}
+
+// Value of lane ^ 1, ^ 2 within a quad, and of the mirrored lane of 8 (DPP).
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp(uint32_t v) {
+    return static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(static_cast<int>(v), CTRL, 0xF, 0xF, true));
+}
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kMirror8 = 0x141;
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) { return __uint_as_float(dpp<CTRL>(__float_as_uint(v))); }
+
+// x / s, correctly rounded, for a bf16 value x and r = RN(1 / s): the product
+// x r corrected once by its exact remainder.  Checked for every mantissa of x
+// and s (2^7 x 2^23 pairs, tests/test_writer_quotient.py); powers of two scale
+// through while s and r are normal and the quotient is far from overflow.  A
+// quotient so small that the remainder underflows (below 2^-40) may be off in
+// its last place, far below the rounding of q + z.
+__device__ __forceinline__ float fast_div(float x, float s, float r) {
+    const float q = __fmul_rn(x, r);
+    return __fmaf_rn(__fmaf_rn(-q, s, x), r, q);
+}
+
 // Quantize the lane's 8 channels `raw` (bf16) of group g of a token (lane lig
 // of the group's 8; rope: the RoPE-key group) and store its codes and
 // metadata at token `off` of the page at `base`.
@@ -65,17 +107,25 @@ __device__ __forceinline__ void quantize_store(const uint4 raw, bool rope, int g
         lo = fminf(lo, x[i]);
         hi = fmaxf(hi, x[i]);
     }
-#pragma unroll
-    for (int d = 1; d < kLanesPerGroup; d <<= 1) {
-        lo = fminf(lo, __shfl_xor(lo, d, kLanesPerGroup));
-        hi = fmaxf(hi, __shfl_xor(hi, d, kLanesPerGroup));
-    }
+    lo = fminf(lo, dpp<kXor1>(lo));
+    hi = fmaxf(hi, dpp<kXor1>(hi));
+    lo = fminf(lo, dpp<kXor2>(lo));
+    hi = fmaxf(hi, dpp<kXor2>(hi));
+    // the quads are uniform by now: the mirrored lane is in the other one
+    lo = fminf(lo, dpp<kMirror8>(lo));
+    hi = fmaxf(hi, dpp<kMirror8>(hi));
 
     const int bits = rope ? 4 : CBITS;
     const float m = static_cast<float>((1 << bits) - 1);
     const float s = __fdiv_rn(fmaxf(__fsub_rn(hi, lo), 1e-8f), m);
+    // One reciprocal per group in place of nine divisions (a correctly rounded
+    // division is about 11 instructions, fast_div 3), where its conditions hold: s
+    // normal with a normal reciprocal, no quotient past 2^60.  Else (a group of
+    // one huge value, or a range that overflows) divisions.
+    const float r = __fdiv_rn(1.0f, s);
+    const bool fast = s < 0x1p100f && fmaxf(fabsf(lo), fabsf(hi)) * r < 0x1p60f;
     // integer zero-point in [0, m]; "+ 0.0f" turns a -0 from rint into +0
-    const float z = fminf(fmaxf(rintf(__fdiv_rn(-lo, s)), 0.0f), m) + 0.0f;
+    const float z = fminf(fmaxf(rintf(fast ? fast_div(-lo, s, r) : __fdiv_rn(-lo, s)), 0.0f), m) + 0.0f;
 
     // Code layout: little-endian 32-bit words of 32 / bits consecutive
     // channels; channel 2i of a word in bits [bits i, bits (i+1)), channel
@@ -83,16 +133,28 @@ __device__ __forceinline__ void quantize_store(const uint4 raw, bool rope, int g
     // pair with one shift and one mask).  A lane's 8 channels fill a 4-bit
     // word, or one half of each 16-bit half of a 2-bit word: the two lanes of
     // a 2-bit word merge their parts.
-    uint32_t packed = 0;
-    const int sh2 = 8 * (lig & 1);
+    // Each half is summed in fp32 (below 2^16, exact) and converted once.
+    float d[8];
+    if (fast) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const float t = __fadd_rn(__fdiv_rn(x[i], s), z);
-        const uint32_t q = static_cast<uint32_t>(fminf(fmaxf(rintf(t), 0.0f), m));
-        const int pos = bits == 4 ? 4 * (i >> 1) : sh2 + 2 * (i >> 1);
-        packed |= q << (pos + 16 * (i & 1));
+        for (int i = 0; i < 8; ++i) d[i] = fast_div(x[i], s, r);
+    } else {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) d[i] = __fdiv_rn(x[i], s);
     }
-    const uint32_t word2 = packed | static_cast<uint32_t>(__shfl_xor(static_cast<int>(packed), 1, kLanesPerGroup));
+    const float radix = rope || CBITS == 4 ? 16.0f : 4.0f;
+    float part[2] = {0.0f, 0.0f};
+#pragma unroll
+    for (int i = 7; i >= 0; --i) {
+        const float q = fminf(fmaxf(rintf(__fadd_rn(d[i], z)), 0.0f), m);
+        part[i & 1] = __fmaf_rn(part[i & 1], radix, q);
+    }
+    uint32_t packed = static_cast<uint32_t>(part[0]) | (static_cast<uint32_t>(part[1]) << 16);
+    uint32_t word2 = 0;
+    if constexpr (CBITS == 2) {
+        const uint32_t shifted = packed << (8 * (lig & 1));
+        word2 = shifted | dpp<kXor1>(shifted);
+    }
 
     if (rope) {
         *reinterpret_cast<uint32_t*>(base + geom.off_cr + off * geom.cr_bytes + lig * 4) = packed;
