@@ -1,7 +1,8 @@
-// Decode attention for few query rows per sequence (up to 32 per wave), the
-// regime of 16 heads and one query token (Appendix F.1, "Native Attention") or
-// of 32 rows, where the 128-row kernel of decode_attn.hip would leave most of
-// every matrix instruction idle.  Same computation and results contract:
+// Decode attention in workgroups of 16 or 32 query rows: the regime of 16 heads
+// and one query token (Appendix F.1, "Native Attention") or of 32 rows, where
+// the kernels of decode_attn.hip would leave most of every matrix instruction
+// idle, and launches of few work items at any number of rows, where they would
+// leave most of the chip idle (choose_shape in internal.h).  Same computation and results contract:
 // absorbed MLA scores z_t = tau (q_lat . C_hat_t + q_rope . K_hat_t), softmax,
 // latent aggregation O = A C_hat (Sec. 2.1, eq. mla_compact), split partials as
 // in Appendix C.5 "Global attention normalization", BF16 protection of sink and
@@ -70,7 +71,6 @@ constexpr int kMaxRows = kNarrowRows;   // rows of the widest wave
 constexpr int kDc = 512;
 constexpr int kQSteps = 18;         // 576 channels / 32 per k-step
 constexpr float kRefSlack = 10.0f;
-constexpr int kCus = 256;           // compute units; one wave per SIMD, four per unit
 constexpr float kLn2 = 0.693147180559945309f;
 
 // LDS tiles, in 16-byte units.  Row r of the fp16 content tile starts at unit
@@ -779,7 +779,13 @@ void narrow_kernel(DecodeArgs a) {
             for (int it = 1; it < n_tiles; ++it) step(it, std::true_type{}, std::true_type{});
             step(n_tiles, std::false_type{}, std::true_type{});
         } else {
-            // raw bf16 rows: both products read the staged tile directly
+            // raw bf16 rows: both products read the staged tile directly.  Each weight
+            // enters the aggregation to 16 significant bits, bf16(w) and the bf16
+            // rounding of the exact residual w - bf16(w) in two products per block,
+            // over protected rows and wherever several waves share a work item
+            // (launches bound by latency, which the second product hardly lengthens);
+            // else the weights are bf16 alone and the normalizer sums them rounded.
+            constexpr bool kPairW = kRing || kW > 1;
             read_q();
             int st_pg = t_begin / P, st_po = t_begin % P, pid_pg = -1, pid = 0;   // next tile to stage
             auto slot_base = [&](int j) { return smem + slot_offset(j, kBfSlots, kBfTileBytes); };
@@ -863,18 +869,14 @@ void narrow_kernel(DecodeArgs a) {
                     }
                 }
                 softmax(it, sc, p);
-                // The weights as bf16 (the BF16 cache; the normalizer sums the
-                // rounded weights), or over protected rows to 16 significant bits:
-                // bf16(w) and the bf16 rounding of the exact residual w - bf16(w),
-                // two products per block.
                 uint32_t ph[kScores / 2], pl[kScores / 2];
 #pragma unroll
                 for (int q = 0; q < kScores / 2; ++q) {
                     ph[q] = pack_bf16x2(p[2 * q], p[2 * q + 1]);
                     const float h0 = __uint_as_float(ph[q] << 16), h1 = __uint_as_float(ph[q] & 0xFFFF0000u);
                     pl[q] = pack_bf16x2(p[2 * q] - h0, p[2 * q + 1] - h1);
-                    l_run += kRing ? p[2 * q] : h0;
-                    l_run += kRing ? p[2 * q + 1] : h1;
+                    l_run += kPairW ? p[2 * q] : h0;
+                    l_run += kPairW ? p[2 * q + 1] : h1;
                 }
                 // aggregation, transposing reads eight (16 rows) or four blocks
                 // ahead of the products
@@ -889,7 +891,7 @@ void narrow_kernel(DecodeArgs a) {
 #pragma unroll
                     for (int m = 0; m < kAccs; ++m) {
                         acc[m] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vb[m % kVAhead], pbh, acc[m], 0, 0, 0);
-                        if constexpr (kRing)
+                        if constexpr (kPairW)
                             acc[m] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vb[m % kVAhead], pbl, acc[m], 0, 0, 0);
                         if (m + kVAhead < kAccs) vb[m % kVAhead] = tr_read(vbase + tr_imm(m + kVAhead));
                     }
@@ -910,7 +912,7 @@ void narrow_kernel(DecodeArgs a) {
 #pragma unroll
                     for (int m = 0; m < kAccs; ++m) {
                         acc[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vb[m % kVAhead], pbh, acc[m], 0, 0, 0);
-                        if constexpr (kRing)
+                        if constexpr (kPairW)
                             acc[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vb[m % kVAhead], pbl, acc[m], 0, 0, 0);
                         if (m + kVAhead < kAccs) vb[m % kVAhead] = vread(m + kVAhead);
                     }
@@ -1129,47 +1131,36 @@ void narrow_kernel(DecodeArgs a) {
     }
 }
 
-// Waves per work item.  A workgroup of kW waves takes kW of a unit's four SIMDs,
-// so 256 work items leave three waves in four idle at kW = 1 and 512 every
-// second one.  Measured (16 rows, one 256-token work item): 21.9, 15.7, 13.6 us at
-// 1, 2, 4 waves; 264 items of 128 tokens: 15.9, 14.0, 14.0 us; past 512 items the
-// extra waves only queue (520 items of 64 tokens: 16.1, 22.3, 27.8 us).
 template <int KIND, bool kProt, int kR>
 void launch_rows(const DecodeArgs& a, hipStream_t stream, const LaunchEvents& ev) {
     const int64_t blocks = decode_workgroups(a.num_work, static_cast<int64_t>(a.s_q) * a.H, kR);
     const dim3 grid(static_cast<unsigned>(blocks));
-    if (blocks <= kCus)
-        dispatch_decode(narrow_kernel<KIND, kProt, kR, 4>, grid, dim3(256), stream, ev, a);
-    else if (blocks <= 2 * kCus)
-        dispatch_decode(narrow_kernel<KIND, kProt, kR, 2>, grid, dim3(128), stream, ev, a);
-    else
-        dispatch_decode(narrow_kernel<KIND, kProt, kR, 1>, grid, dim3(64), stream, ev, a);
+    switch (narrow_waves(blocks)) {
+        case 4: dispatch_decode(narrow_kernel<KIND, kProt, kR, 4>, grid, dim3(256), stream, ev, a); break;
+        case 2: dispatch_decode(narrow_kernel<KIND, kProt, kR, 2>, grid, dim3(128), stream, ev, a); break;
+        default: dispatch_decode(narrow_kernel<KIND, kProt, kR, 1>, grid, dim3(64), stream, ev, a); break;
+    }
 }
 
-// One 32-row wave for 17 to 32 rows: each tile is dequantized once, where two
-// 16-row waves would do it twice (1.4 us per 16 tokens, against twice 1.5).
-// While two 16-row workgroups per work item still leave every workgroup a unit
-// of its own, those are shorter (fixed costs of about 9 us against 13).
 template <int KIND, bool kProt>
-void launch_kind(const DecodeArgs& a, hipStream_t stream, const LaunchEvents& ev) {
-    const int rows = a.s_q * a.H;
-    if (rows <= 16 || decode_workgroups(a.num_work, rows, 16) <= kCus) launch_rows<KIND, kProt, 16>(a, stream, ev);
+void launch_kind(const DecodeArgs& a, RowShape shape, hipStream_t stream, const LaunchEvents& ev) {
+    if (shape == ROWS_16) launch_rows<KIND, kProt, 16>(a, stream, ev);
     else launch_rows<KIND, kProt, kMaxRows>(a, stream, ev);
 }
 
 template <bool kProt>
-hipError_t launch(CacheKind kind, const DecodeArgs& a, hipStream_t stream) {
+hipError_t launch(CacheKind kind, const DecodeArgs& a, RowShape shape, hipStream_t stream) {
     if (a.num_work == 0) return hipSuccess;
     const LaunchEvents ev = take_launch_events();
     static_assert(kNarrowThreads == 64 && kNarrowRowsPerBlock == 16, "the host checks the largest launch");
     switch (kind) {
-        case KIND_C4R4: launch_kind<KIND_C4R4, kProt>(a, stream, ev); break;
-        case KIND_C2R4: launch_kind<KIND_C2R4, kProt>(a, stream, ev); break;
-        case KIND_C4R4P: launch_kind<KIND_C4R4P, kProt>(a, stream, ev); break;
-        case KIND_C2R4P: launch_kind<KIND_C2R4P, kProt>(a, stream, ev); break;
+        case KIND_C4R4: launch_kind<KIND_C4R4, kProt>(a, shape, stream, ev); break;
+        case KIND_C2R4: launch_kind<KIND_C2R4, kProt>(a, shape, stream, ev); break;
+        case KIND_C4R4P: launch_kind<KIND_C4R4P, kProt>(a, shape, stream, ev); break;
+        case KIND_C2R4P: launch_kind<KIND_C2R4P, kProt>(a, shape, stream, ev); break;
         case KIND_BF16:
             if constexpr (kProt) return hipErrorInvalidValue;
-            else launch_kind<KIND_BF16, false>(a, stream, ev);
+            else launch_kind<KIND_BF16, false>(a, shape, stream, ev);
             break;
     }
     return hipGetLastError();
@@ -1177,12 +1168,12 @@ hipError_t launch(CacheKind kind, const DecodeArgs& a, hipStream_t stream) {
 
 }  // namespace
 
-hipError_t launch_decode_narrow(CacheKind kind, const DecodeArgs& a, hipStream_t stream) {
-    return launch<false>(kind, a, stream);
+hipError_t launch_decode_narrow(CacheKind kind, const DecodeArgs& a, RowShape shape, hipStream_t stream) {
+    return launch<false>(kind, a, shape, stream);
 }
 
-hipError_t launch_decode_narrow_protected(CacheKind kind, const DecodeArgs& a, hipStream_t stream) {
-    return launch<true>(kind, a, stream);
+hipError_t launch_decode_narrow_protected(CacheKind kind, const DecodeArgs& a, RowShape shape, hipStream_t stream) {
+    return launch<true>(kind, a, shape, stream);
 }
 
 }  // namespace mla

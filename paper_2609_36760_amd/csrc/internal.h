@@ -100,9 +100,12 @@ LaunchEvents take_launch_events();
 
 hipError_t launch_lowbit_append(const AppendArgs& a, hipStream_t stream);
 hipError_t launch_bf16_append(const AppendArgs& a, hipStream_t stream);
-hipError_t launch_decode(CacheKind kind, const DecodeArgs& a, hipStream_t stream);
-hipError_t launch_decode_protected(CacheKind kind, const DecodeArgs& a, hipStream_t stream);
-// The same computation for few query rows (s_q * H <= kNarrowRows): 16 rows per one-wave workgroup.
+// Query rows of a workgroup: 16 or 32 (decode_narrow.hip, one to four waves on
+// one row block) or 64 or 128 (decode_attn.hip, four waves on one tile).
+enum RowShape { ROWS_16 = 16, ROWS_32 = 32, ROWS_64 = 64, ROWS_128 = 128 };
+hipError_t launch_decode(CacheKind kind, const DecodeArgs& a, RowShape shape, hipStream_t stream);
+hipError_t launch_decode_protected(CacheKind kind, const DecodeArgs& a, RowShape shape, hipStream_t stream);
+// The same computation in 16- or 32-row workgroups.
 constexpr int kNarrowRows = 32;
 
 // Launch shapes, for the host's size checks (each kernel file asserts its own
@@ -126,8 +129,68 @@ constexpr int64_t decode_workgroups(int64_t num_work, int64_t rows, int64_t rows
     return (num_work + kWorkGroupRound - 1) / kWorkGroupRound * kWorkGroupRound *
            ((rows + rows_per_block - 1) / rows_per_block);
 }
-hipError_t launch_decode_narrow(CacheKind kind, const DecodeArgs& a, hipStream_t stream);
-hipError_t launch_decode_narrow_protected(CacheKind kind, const DecodeArgs& a, hipStream_t stream);
+hipError_t launch_decode_narrow(CacheKind kind, const DecodeArgs& a, RowShape shape, hipStream_t stream);
+hipError_t launch_decode_narrow_protected(CacheKind kind, const DecodeArgs& a, RowShape shape, hipStream_t stream);
+
+// Waves per 16- or 32-row workgroup: they share the work item's keys.  A
+// workgroup of w waves takes w of a compute unit's four SIMDs, so up to 256
+// workgroups four waves cost nothing, up to 512 two; past that the extra waves
+// only queue (16 rows, 520 work items of 64 tokens: 16.1, 22.3, 27.8 us at 1, 2, 4).
+constexpr int kCus = 256;
+constexpr int narrow_waves(int64_t blocks) { return blocks <= kCus ? 4 : blocks <= 2 * kCus ? 2 : 1; }
+
+// The shape a launch runs in: the shortest by a cost of rounds x (fixed + tiles
+// x per-tile) us, tiles of 32 tokens per wave.  Fewer rows per workgroup repeat
+// the dequantization (and the reads) for every row block, but a launch of few
+// work items leaves most of the chip to them; the constants are fits to kernel
+// times over 4 to 512 work items of 64 to 2 048 tokens at 64, 128 and 256 rows
+// (INT4; INT2 within 5 %).  For 128 rows, at 16 / 32 / 128 rows per workgroup:
+//   16 items of 512 tokens    21.6 /  28.3 /  39.3 us
+//   64 items of 512           33.0 /  31.2 /  42.1
+//   64 items of 2 048         83.2 /  66.4 / 114.9
+//   128 items of 64           19.2 /  21.4 /  19.9
+//   128 items of 2 048       148.7 / 110.9 / 117.7
+//   256 items of 512          89.3 /  67.0 /  51.4
+// and for 64 rows, at 16 / 32 / 64:
+//   128 items of 512          31.8 /  30.7 /  38.7
+//   256 items of 512          47.9 /  42.8 /  44.0
+//   272 items of 64           25.2 /  21.9 /  33.6 (the 64-row ones in two rounds)
+//   272 items of 2 048       269.9 / 198.5 / 188.5
+struct ShapeCost { float fixed, per_tile; };
+inline RowShape choose_shape(bool lowbit, int64_t rows, int64_t num_work, int64_t tokens) {
+    // [16 rows, 32 rows][4, 2, 1 waves], then 64 and 128 rows
+    static constexpr ShapeCost kNarrowLowbit[2][3] = {{{12.0f, 0.62f}, {13.5f, 1.07f}, {14.8f, 2.08f}},
+                                                      {{17.5f, 0.72f}, {18.5f, 1.45f}, {20.0f, 2.95f}}};
+    static constexpr ShapeCost kNarrowBf16[2][3] = {{{11.5f, 0.82f}, {13.0f, 1.8f}, {15.5f, 3.4f}},
+                                                    {{15.5f, 1.05f}, {18.5f, 2.2f}, {21.0f, 3.9f}}};
+    static constexpr ShapeCost kWide[2][2] = {{{18.5f, 1.25f}, {17.5f, 1.6f}}, {{17.5f, 1.1f}, {17.5f, 1.4f}}};
+    if (rows <= ROWS_16) return ROWS_16;
+    RowShape best = ROWS_128;
+    float least = 0.0f;
+    const float n = static_cast<float>((tokens + 31) / 32);
+    if (rows > ROWS_32) {
+        const bool half = rows <= ROWS_64;
+        const ShapeCost c = kWide[lowbit ? 0 : 1][half ? 0 : 1];
+        best = half ? ROWS_64 : ROWS_128;
+        const int64_t blocks = decode_workgroups(num_work, rows, kDecodeRowsPerBlock);
+        least = static_cast<float>((blocks + kCus - 1) / kCus) * (c.fixed + n * c.per_tile);
+    }
+    for (int i = 0; i < 2; ++i) {
+        const int64_t blocks = decode_workgroups(num_work, rows, i == 0 ? ROWS_16 : ROWS_32);
+        const int w = narrow_waves(blocks);
+        // the bf16 weights of one-wave workgroups (decode_narrow.hip) are left to
+        // launches of at most 32 rows
+        if (!lowbit && w == 1 && rows > ROWS_32) continue;
+        const ShapeCost c = (lowbit ? kNarrowLowbit : kNarrowBf16)[i][w == 4 ? 0 : w == 2 ? 1 : 2];
+        const float rounds = static_cast<float>((blocks * w + 4 * kCus - 1) / (4 * kCus));
+        const float cost = rounds * (c.fixed + n * c.per_tile);
+        if ((rows <= ROWS_32 && i == 0) || cost < least) {
+            least = cost;
+            best = i == 0 ? ROWS_16 : ROWS_32;
+        }
+    }
+    return best;
+}
 hipError_t launch_lowbit_append_protected(const AppendArgs& a, hipStream_t stream);
 // num_splits (split_indptr[B]) chooses between one wave per row and four waves sharing a row.
 hipError_t launch_combine(const CombineArgs& a, int32_t num_splits, hipStream_t stream);

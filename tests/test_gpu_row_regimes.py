@@ -1,10 +1,11 @@
 """GPU parity where the decode kernels change shape with the number of query
 rows and of work items.
 
-Up to 32 rows a wave owns 16 or 32 of them, over tiles of 32 or 16 tokens; with
-few workgroups a work item's keys are shared by four or two waves that merge
-their parts; 33 to 64 rows run in 64-row workgroups whose waves split each
-tile's tokens in two halves.  The lengths sit on the edges of those tiles and
+A wave of the few-row kernel owns 16 or 32 rows, over tiles of 32 or 16 tokens;
+with few workgroups a work item's keys are shared by four or two waves that
+merge their parts.  It serves up to 32 rows, and any number while the work
+items are few; enough of them run in 64-row workgroups (33 to 64 rows) whose
+waves split each tile's tokens in two halves, or in 128-row ones.  The lengths sit on the edges of those tiles and
 parts (one key, one token short of and past a 16- or 32-token tile, parts with
 no key at all), the work-item counts on both sides of 256 and 512, and single
 ranges run past the 64 page ids that a wave holds at a time.  Every output of
@@ -20,6 +21,7 @@ pytestmark = pytest.mark.gpu
 
 EDGES = [2, 15, 16, 17, 31, 32, 33, 47, 48, 49, 63, 64, 65, 97, 129, 160]
 SHORT = [33, 2, 40, 17]
+FULL = SHORT * 60                # with EDGES: 256 sequences
 CASES = [
     # (name, H, s_q, lens, cache, split, page, (sink, recent) or None, sequences compared: None all)
     ("r16_four_waves", 16, 1, EDGES, "c4", 0, 64, None, None),
@@ -41,13 +43,25 @@ CASES = [
     ("r16_pages", 16, 1, [2200] + SHORT * 130, "c4", 0, 32, None, [0, 1]),
     ("r32_pages", 16, 2, [2200] + SHORT * 130, "c4", 0, 32, None, [0, 1]),
     ("r16_pages_four_waves", 16, 1, [8400, 33], "c4", 0, 32, None, None),
-    # 64-row workgroups, token-split waves
-    ("r64_nosplit", 64, 1, EDGES, "c4", 0, 64, None, None),
-    ("r64_split32_sq2", 32, 2, EDGES, "c2", 32, 64, None, None),
-    ("r48_paper_split96", 48, 1, EDGES, "c4paper", 96, 32, None, None),
-    ("r64_prot_split64", 64, 1, EDGES + [300], "c4", 64, 64, (4, 128), None),
-    ("r64_bf16_sq2", 32, 2, EDGES, "bf16", 64, 64, None, None),
-    ("r48_bf16", 48, 1, EDGES, "bf16", 0, 64, None, None),
+    # many row blocks of 16 or 32 rows: few work items at 64 to 256 rows
+    ("r64_few_items", 64, 1, EDGES, "c4", 0, 64, None, None),
+    ("r256_few_items_prot", 128, 2, [2, 33, 300], "c4", 64, 64, (4, 128), None),
+    ("r80_few_items_bf16", 80, 1, EDGES, "bf16", 96, 64, None, None),
+    ("r128_mid_items_paper", 128, 1, EDGES + SHORT * 12, "c2paper", 0, 64, None, list(range(18))),
+    # 256 work items of up to 192 tokens fill the chip with 64-row workgroups,
+    # whose waves split each tile's tokens
+    ("r64_nosplit", 64, 1, EDGES + FULL, "c4", 0, 64, None, list(range(18))),
+    ("r64_split160_sq2", 32, 2, EDGES + FULL, "c2", 160, 64, None, list(range(18))),
+    ("r48_paper", 48, 1, EDGES + FULL, "c4paper", 0, 32, None, list(range(18))),
+    ("r64_prot", 64, 1, EDGES + FULL, "c4", 0, 64, (3, 20), list(range(18))),
+    ("r64_bf16_sq2", 32, 2, EDGES + FULL, "bf16", 0, 64, None, list(range(18))),
+    ("r48_bf16", 48, 1, EDGES + FULL, "bf16", 0, 64, None, list(range(18))),
+    # and with 128-row ones
+    ("r128_nosplit", 128, 1, EDGES + FULL, "c4", 0, 64, None, list(range(18))),
+    ("r128_split96_paper", 128, 1, EDGES + FULL, "c2paper", 96, 64, None, list(range(18))),
+    ("r256_sq2", 128, 2, EDGES + FULL, "c2", 0, 64, None, list(range(18))),
+    ("r128_prot_split96", 128, 1, EDGES + FULL, "c4", 96, 64, (3, 20), list(range(18))),
+    ("r160_bf16_sq2", 80, 2, EDGES + FULL, "bf16", 0, 64, None, list(range(18))),
 ]
 
 
