@@ -128,17 +128,29 @@ def mla_time_next_decode_launch(start, stop) -> None:
 
 
 def _ptr(t):
-    if t is None:
-        return None
-    if isinstance(t, int):
-        return t
-    return t.data_ptr()
+    try:
+        return t.data_ptr()
+    except AttributeError:
+        if t is None or isinstance(t, int):
+            return t
+        raise
+
+
+_torch = None
 
 
 def _stream(stream):
+    """Raw handle of ``stream``, or of torch's current stream on the current
+    device: asked for directly, which takes 0.2 us where building a
+    ``torch.cuda.Stream`` takes 2.8 (a whole append call took 7.2 us)."""
+    global _torch
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        if _torch is None:
+            import torch
+            if not torch.cuda.is_initialized():
+                return torch.cuda.current_stream().cuda_stream
+            _torch = torch
+        return _torch._C._cuda_getCurrentRawStream(_torch._C._cuda_getDevice())
     return stream if isinstance(stream, int) else stream.cuda_stream
 
 
