@@ -1427,36 +1427,38 @@ namespace {
 // per 32-token tile: 1.0-1.3 us against 1.6; 256 work items of 480, 960 and 1 920
 // tokens: 39.7, 56.1, 94.4 us against 42.8, 67.4, 114.1.
 template <int KIND, bool kProt>
-void launch_kind(const DecodeArgs& a, RowShape shape, hipStream_t stream, const LaunchEvents& ev) {
-    const int64_t blocks = decode_workgroups(a.num_work, static_cast<int64_t>(a.s_q) * a.H, shape);
+void launch_kind(const DecodeArgs& a, hipStream_t stream, const LaunchEvents& ev) {
+    const int64_t blocks = decode_workgroups(a.num_work, static_cast<int64_t>(a.s_q) * a.H, a.shape);
     const dim3 grid(static_cast<unsigned>(blocks)), block(kThreads);
-    if (shape == ROWS_64) dispatch_decode(decode_kernel<KIND, kProt, 2>, grid, block, stream, ev, a);
+    if (a.shape == ROWS_64) dispatch_decode(decode_kernel<KIND, kProt, 2>, grid, block, stream, ev, a);
     else dispatch_decode(decode_kernel<KIND, kProt, 1>, grid, block, stream, ev, a);
 }
 
 }  // namespace
 
-hipError_t launch_decode(CacheKind kind, const DecodeArgs& a, RowShape shape, hipStream_t stream) {
+hipError_t launch_decode(CacheKind kind, const DecodeArgs& a, hipStream_t stream) {
     if (a.num_work == 0) return hipSuccess;
+    if (a.shape <= ROWS_32) return launch_decode_narrow(kind, a, stream);
     const LaunchEvents ev = take_launch_events();
     switch (kind) {
-        case KIND_C4R4: launch_kind<KIND_C4R4, false>(a, shape, stream, ev); break;
-        case KIND_C2R4: launch_kind<KIND_C2R4, false>(a, shape, stream, ev); break;
-        case KIND_C4R4P: launch_kind<KIND_C4R4P, false>(a, shape, stream, ev); break;
-        case KIND_C2R4P: launch_kind<KIND_C2R4P, false>(a, shape, stream, ev); break;
-        case KIND_BF16: launch_kind<KIND_BF16, false>(a, shape, stream, ev); break;
+        case KIND_C4R4: launch_kind<KIND_C4R4, false>(a, stream, ev); break;
+        case KIND_C2R4: launch_kind<KIND_C2R4, false>(a, stream, ev); break;
+        case KIND_C4R4P: launch_kind<KIND_C4R4P, false>(a, stream, ev); break;
+        case KIND_C2R4P: launch_kind<KIND_C2R4P, false>(a, stream, ev); break;
+        case KIND_BF16: launch_kind<KIND_BF16, false>(a, stream, ev); break;
     }
     return hipGetLastError();
 }
 
-hipError_t launch_decode_protected(CacheKind kind, const DecodeArgs& a, RowShape shape, hipStream_t stream) {
+hipError_t launch_decode_protected(CacheKind kind, const DecodeArgs& a, hipStream_t stream) {
     if (a.num_work == 0) return hipSuccess;
+    if (a.shape <= ROWS_32) return launch_decode_narrow_protected(kind, a, stream);
     const LaunchEvents ev = take_launch_events();
     switch (kind) {
-        case KIND_C4R4: launch_kind<KIND_C4R4, true>(a, shape, stream, ev); break;
-        case KIND_C2R4: launch_kind<KIND_C2R4, true>(a, shape, stream, ev); break;
-        case KIND_C4R4P: launch_kind<KIND_C4R4P, true>(a, shape, stream, ev); break;
-        case KIND_C2R4P: launch_kind<KIND_C2R4P, true>(a, shape, stream, ev); break;
+        case KIND_C4R4: launch_kind<KIND_C4R4, true>(a, stream, ev); break;
+        case KIND_C2R4: launch_kind<KIND_C2R4, true>(a, stream, ev); break;
+        case KIND_C4R4P: launch_kind<KIND_C4R4P, true>(a, stream, ev); break;
+        case KIND_C2R4P: launch_kind<KIND_C2R4P, true>(a, stream, ev); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

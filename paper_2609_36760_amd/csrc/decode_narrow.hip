@@ -1143,24 +1143,24 @@ void launch_rows(const DecodeArgs& a, hipStream_t stream, const LaunchEvents& ev
 }
 
 template <int KIND, bool kProt>
-void launch_kind(const DecodeArgs& a, RowShape shape, hipStream_t stream, const LaunchEvents& ev) {
-    if (shape == ROWS_16) launch_rows<KIND, kProt, 16>(a, stream, ev);
+void launch_kind(const DecodeArgs& a, hipStream_t stream, const LaunchEvents& ev) {
+    if (a.shape == ROWS_16) launch_rows<KIND, kProt, 16>(a, stream, ev);
     else launch_rows<KIND, kProt, kMaxRows>(a, stream, ev);
 }
 
 template <bool kProt>
-hipError_t launch(CacheKind kind, const DecodeArgs& a, RowShape shape, hipStream_t stream) {
+hipError_t launch(CacheKind kind, const DecodeArgs& a, hipStream_t stream) {
     if (a.num_work == 0) return hipSuccess;
     const LaunchEvents ev = take_launch_events();
     static_assert(kNarrowThreads == 64 && kNarrowRowsPerBlock == 16, "the host checks the largest launch");
     switch (kind) {
-        case KIND_C4R4: launch_kind<KIND_C4R4, kProt>(a, shape, stream, ev); break;
-        case KIND_C2R4: launch_kind<KIND_C2R4, kProt>(a, shape, stream, ev); break;
-        case KIND_C4R4P: launch_kind<KIND_C4R4P, kProt>(a, shape, stream, ev); break;
-        case KIND_C2R4P: launch_kind<KIND_C2R4P, kProt>(a, shape, stream, ev); break;
+        case KIND_C4R4: launch_kind<KIND_C4R4, kProt>(a, stream, ev); break;
+        case KIND_C2R4: launch_kind<KIND_C2R4, kProt>(a, stream, ev); break;
+        case KIND_C4R4P: launch_kind<KIND_C4R4P, kProt>(a, stream, ev); break;
+        case KIND_C2R4P: launch_kind<KIND_C2R4P, kProt>(a, stream, ev); break;
         case KIND_BF16:
             if constexpr (kProt) return hipErrorInvalidValue;
-            else launch_kind<KIND_BF16, false>(a, shape, stream, ev);
+            else launch_kind<KIND_BF16, false>(a, stream, ev);
             break;
     }
     return hipGetLastError();
@@ -1168,12 +1168,12 @@ hipError_t launch(CacheKind kind, const DecodeArgs& a, RowShape shape, hipStream
 
 }  // namespace
 
-hipError_t launch_decode_narrow(CacheKind kind, const DecodeArgs& a, RowShape shape, hipStream_t stream) {
-    return launch<false>(kind, a, shape, stream);
+hipError_t launch_decode_narrow(CacheKind kind, const DecodeArgs& a, hipStream_t stream) {
+    return launch<false>(kind, a, stream);
 }
 
-hipError_t launch_decode_narrow_protected(CacheKind kind, const DecodeArgs& a, RowShape shape, hipStream_t stream) {
-    return launch<true>(kind, a, shape, stream);
+hipError_t launch_decode_narrow_protected(CacheKind kind, const DecodeArgs& a, hipStream_t stream) {
+    return launch<true>(kind, a, stream);
 }
 
 }  // namespace mla

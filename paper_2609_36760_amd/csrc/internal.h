@@ -46,7 +46,12 @@ struct AppendArgs {
 // Low-bit kinds: content bits and metadata storage (P: the paper's record).
 enum CacheKind { KIND_C4R4 = 0, KIND_C2R4 = 1, KIND_BF16 = 2, KIND_C4R4P = 3, KIND_C2R4P = 4 };
 
+// Query rows of a workgroup: 16 or 32 (decode_narrow.hip, one to four waves on
+// one row block) or 64 or 128 (decode_attn.hip, four waves on one tile).
+enum RowShape { ROWS_16 = 16, ROWS_32 = 32, ROWS_64 = 64, ROWS_128 = 128 };
+
 struct DecodeArgs {
+    RowShape shape;         // of the launch (choose_shape)
     const uint16_t* q_lat;
     const uint16_t* q_rope;
     const uint8_t* cache;
@@ -100,11 +105,9 @@ LaunchEvents take_launch_events();
 
 hipError_t launch_lowbit_append(const AppendArgs& a, hipStream_t stream);
 hipError_t launch_bf16_append(const AppendArgs& a, hipStream_t stream);
-// Query rows of a workgroup: 16 or 32 (decode_narrow.hip, one to four waves on
-// one row block) or 64 or 128 (decode_attn.hip, four waves on one tile).
-enum RowShape { ROWS_16 = 16, ROWS_32 = 32, ROWS_64 = 64, ROWS_128 = 128 };
-hipError_t launch_decode(CacheKind kind, const DecodeArgs& a, RowShape shape, hipStream_t stream);
-hipError_t launch_decode_protected(CacheKind kind, const DecodeArgs& a, RowShape shape, hipStream_t stream);
+// (launch_decode hands launches of 16- and 32-row shape on to the narrow kernel)
+hipError_t launch_decode(CacheKind kind, const DecodeArgs& a, hipStream_t stream);
+hipError_t launch_decode_protected(CacheKind kind, const DecodeArgs& a, hipStream_t stream);
 // The same computation in 16- or 32-row workgroups.
 constexpr int kNarrowRows = 32;
 
@@ -129,8 +132,8 @@ constexpr int64_t decode_workgroups(int64_t num_work, int64_t rows, int64_t rows
     return (num_work + kWorkGroupRound - 1) / kWorkGroupRound * kWorkGroupRound *
            ((rows + rows_per_block - 1) / rows_per_block);
 }
-hipError_t launch_decode_narrow(CacheKind kind, const DecodeArgs& a, RowShape shape, hipStream_t stream);
-hipError_t launch_decode_narrow_protected(CacheKind kind, const DecodeArgs& a, RowShape shape, hipStream_t stream);
+hipError_t launch_decode_narrow(CacheKind kind, const DecodeArgs& a, hipStream_t stream);
+hipError_t launch_decode_narrow_protected(CacheKind kind, const DecodeArgs& a, hipStream_t stream);
 
 // Waves per 16- or 32-row workgroup: they share the work item's keys.  A
 // workgroup of w waves takes w of a compute unit's four SIMDs, so up to 256
@@ -178,13 +181,14 @@ inline RowShape choose_shape(bool lowbit, int64_t rows, int64_t num_work, int64_
     for (int i = 0; i < 2; ++i) {
         const int64_t blocks = decode_workgroups(num_work, rows, i == 0 ? ROWS_16 : ROWS_32);
         const int w = narrow_waves(blocks);
+        if (blocks * w * kNarrowThreads > kMaxDispatchItems) continue;      // (decode_fits checked the widest shape)
         // the bf16 weights of one-wave workgroups (decode_narrow.hip) are left to
         // launches of at most 32 rows
         if (!lowbit && w == 1 && rows > ROWS_32) continue;
         const ShapeCost c = (lowbit ? kNarrowLowbit : kNarrowBf16)[i][w == 4 ? 0 : w == 2 ? 1 : 2];
         const float rounds = static_cast<float>((blocks * w + 4 * kCus - 1) / (4 * kCus));
         const float cost = rounds * (c.fixed + n * c.per_tile);
-        if ((rows <= ROWS_32 && i == 0) || cost < least) {
+        if (least == 0.0f || cost < least) {
             least = cost;
             best = i == 0 ? ROWS_16 : ROWS_32;
         }

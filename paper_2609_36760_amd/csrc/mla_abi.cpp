@@ -255,8 +255,8 @@ int decode_common(const mla_cache_format* f, bool lowbit, const uint16_t* q_lat,
                                 : f->c_bits == 4 ? (paper ? mla::KIND_C4R4P : mla::KIND_C4R4)
                                                  : (paper ? mla::KIND_C2R4P : mla::KIND_C2R4);
     const int64_t most = split_tokens != 0 ? split_tokens : static_cast<int64_t>(max_pages_per_seq) * f->page_size;
-    const mla::RowShape shape = mla::choose_shape(lowbit, static_cast<int64_t>(s_q) * H, a.num_work, most);
-    const bool narrow = shape <= mla::ROWS_32;
+    a.shape = mla::choose_shape(lowbit, static_cast<int64_t>(s_q) * H, a.num_work, most);
+    const bool narrow = s_q * H <= mla::kNarrowRows;
     if (nt != nullptr && B > 0) {
         // the workgroups that read a new token write it inside the decode launch
         a.new_c = nt->c_kv;
@@ -266,15 +266,14 @@ int decode_common(const mla_cache_format* f, bool lowbit, const uint16_t* q_lat,
         a.new_slots = nt->slot_mapping;
     }
     if (pd == nullptr)
-        return hip_status(narrow ? mla::launch_decode_narrow(kind, a, shape, stream)
-                                 : mla::launch_decode(kind, a, shape, stream));
+        return hip_status(narrow ? mla::launch_decode_narrow(kind, a, stream) : mla::launch_decode(kind, a, stream));
     a.prot = static_cast<const uint8_t*>(pd->prot);
     a.num_prot = pd->num_prot;
     a.prot_slot = pd->prot_slot;
     a.sink = pd->policy->sink;
     a.recent = pd->policy->recent;
-    return hip_status(narrow ? mla::launch_decode_narrow_protected(kind, a, shape, stream)
-                             : mla::launch_decode_protected(kind, a, shape, stream));
+    return hip_status(narrow ? mla::launch_decode_narrow_protected(kind, a, stream)
+                             : mla::launch_decode_protected(kind, a, stream));
 }
 
 }  // namespace
