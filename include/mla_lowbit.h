@@ -211,7 +211,7 @@ int mla_lowbit_decode_attn(const mla_cache_format* f,
  * Same computation over a BF16 cache (the unquantized comparison; row layout
  * in mla_bf16_page_bytes).  Arguments as for mla_lowbit_decode_attn.  The
  * products run in bf16 (cache rows and queries exact), the softmax weights
- * rounded to bf16.  With split partials, the cache values must lie within the
+ * rounded to bf16 (in launches of few work items to 16 significant bits).  With split partials, the cache values must lie within the
  * fp16 range (part_o is fp16).
  */
 int mla_bf16_decode_attn(const mla_cache_format* f,
