@@ -765,8 +765,9 @@ void decode_kernel(DecodeArgs a) {
         const bool small_lane = wave_u < 2 || lane < 8;
 
         // Load k of the tile starting at token t0 (offset po in page pid), into
-        // the slot at LDS address slot_lds.
-        auto issue = [&](int k, int pid, int t0, int po, uint32_t slot_lds) __attribute__((always_inline)) {
+        // the slot at LDS address slot_lds.  Packed tokens of the tile below `first`
+        // read token `first`.
+        auto issue = [&](int k, int pid, int t0, int po, uint32_t slot_lds, uint32_t first) __attribute__((always_inline)) {
             const int nvalid = min(t_end - t0, kTile);
             if constexpr (kRing) {
                 // protected position order: the sink rows, then the window from the ring
@@ -786,10 +787,10 @@ void decode_kernel(DecodeArgs a) {
                 const uint32_t nv1 = static_cast<uint32_t>(nvalid - 1);
                 if constexpr (C::lowbit) {
                     if (k < C::code_rounds) {
-                        const uint32_t tok = min(c_tok + static_cast<uint32_t>(k * (kThreads / cpt)), nv1);
+                        const uint32_t tok = min(max(c_tok + static_cast<uint32_t>(k * (kThreads / cpt)), first), nv1);
                         dma16_m0(page + upo * C::cc, tok * C::cc + c_col, slot_lds + (k * kThreads + wave_u * 64) * 16);
                     } else if (small_lane) {
-                        dma16_m0(page + (static_cast<uint32_t>(s_reg) + (upo << s_shift)), (min(s_tok, nv1) << 5) + s_col,
+                        dma16_m0(page + (static_cast<uint32_t>(s_reg) + (upo << s_shift)), (min(wave_u < 2 ? max(s_tok, first) : s_tok, nv1) << 5) + s_col,
                                  slot_lds + dst_small);
                     }
                 } else {
@@ -882,12 +883,18 @@ void decode_kernel(DecodeArgs a) {
             }
         }
         if constexpr (!kRing) wait_page_ids3(pids[0], pids[1], pids[2]);
+        // Masked tokens below t_lo (the sink, in the first tile) are not loaded:
+        // they enter the aggregation with weight 0, and one that is new in this
+        // launch is written by the work item of the protected rows, or by this one
+        // for its later tiles; nothing orders that with these loads (0 x the stale
+        // bytes can be NaN).  (A tile past the end is staged for nothing.)
+        const uint32_t first_lo = kProt && C::lowbit ? static_cast<uint32_t>(max(t_lo - t_begin, 0)) : 0u;
 #pragma unroll
         for (int j = 0; j < C::D; ++j) {
             if (j < n_tiles) {
                 const int t0 = t_begin + j * kTile;
 #pragma unroll
-                for (int k = 0; k < C::loads; ++k) issue(k, pids[j], t0, t0 % P, stage_slot(j));
+                for (int k = 0; k < C::loads; ++k) issue(k, pids[j], t0, t0 % P, stage_slot(j), j == 0 ? first_lo : 0);
             }
         }
         q_round(0);
@@ -1180,7 +1187,7 @@ void decode_kernel(DecodeArgs a) {
                         // the staging of tile it+D, one load per kStageGap k-steps
                         const int k = (stp - kStageSlot0) / kStageGap;
                         if (stp >= kStageSlot0 && (stp - kStageSlot0) % kStageGap == 0 && k < C::loads)
-                            issue(k, pid, cur_t0, cur_po, stage_slot(kStageQ));
+                            issue(k, pid, cur_t0, cur_po, stage_slot(kStageQ), 0);
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 }
@@ -1188,7 +1195,7 @@ void decode_kernel(DecodeArgs a) {
 #pragma unroll
                 for (int q = 0; q < kPieces; ++q) softmax_piece(q);
 #pragma unroll
-                for (int k = 0; k < C::loads; ++k) issue(k, pid, cur_t0, cur_po, stage_slot(kStageQ));
+                for (int k = 0; k < C::loads; ++k) issue(k, pid, cur_t0, cur_po, stage_slot(kStageQ), 0);
             }
             if constexpr (kQK) {
 #pragma unroll

@@ -544,8 +544,9 @@ void narrow_kernel(DecodeArgs a) {
             const uint8_t* page = nullptr;
             uint32_t oc[kNB], orc[kNB], om[kNB], orm[kNB];
             // page and lane offsets of tile j, and the cursor's move to the next
-            // tile (past the end it stays on the last, which is then read again)
-            auto locate = [&](int j) __attribute__((always_inline)) {
+            // tile (past the end it stays on the last, which is then read again for
+            // nothing).  Tokens of the tile below `first` read token `first`.
+            auto locate = [&](int j, int first) __attribute__((always_inline)) {
                 const int t0 = t_begin + min(j, n_tiles - 1) * kTok;
                 const int last = min(t_end - t0, kTok) - 1;     // tokens past it re-read it
                 if (pg - pid_base == 64) {
@@ -557,7 +558,7 @@ void narrow_kernel(DecodeArgs a) {
                 page = a.cache + static_cast<uint64_t>(static_cast<uint32_t>(pid)) * static_cast<uint32_t>(a.g.page_bytes);
 #pragma unroll
                 for (int nb = 0; nb < kNB; ++nb) {
-                    const uint32_t t = static_cast<uint32_t>(po + min(16 * nb + li, last));
+                    const uint32_t t = static_cast<uint32_t>(po + min(max(16 * nb + li, first), last));
                     oc[nb] = t * C::cc + (C::cbits == 4 ? 16 : 8) * g;
                     orc[nb] = static_cast<uint32_t>(a.g.off_cr) + t * 32 + 8 * g;
                     om[nb] = static_cast<uint32_t>(a.g.off_mc) + t * 32 + (C::pmeta ? 0 : 4 * (g >> 1));
@@ -636,7 +637,11 @@ void narrow_kernel(DecodeArgs a) {
             // the page ids' round trip overlaps the query loads' issue
             read_q();
             __builtin_amdgcn_sched_barrier(0);
-            locate(0);
+            // Masked tokens below t_lo (the sink, in the first tile) are not loaded:
+            // they enter the aggregation with weight 0, and one that is new in this
+            // launch is written by the wave of the protected rows, which nothing
+            // orders with this wave's loads (0 x the stale bytes can be NaN).
+            locate(0, kProt ? max(t_lo - t_begin, 0) : 0);
 #pragma unroll
             for (int j = 0; j < 4; ++j) load_slice(j);
             load_rope();
@@ -677,7 +682,7 @@ void narrow_kernel(DecodeArgs a) {
                 for (int nb = 0; nb < kNB; ++nb)
 #pragma unroll
                     for (int r = 0; r < kNR; ++r) s[nb][r] = f32x4{};
-                if constexpr (kQK) locate(it + 1);
+                if constexpr (kQK) locate(it + 1, 0);
                 if constexpr (kPV) {
 #pragma unroll
                     for (int m = 0; m < kVAhead; ++m) vb[m] = vread(m);

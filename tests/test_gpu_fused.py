@@ -121,6 +121,36 @@ def test_protected_append_decode_matches_separate_calls(case):
           flush=True)
 
 
+@pytest.mark.parametrize("split", [0, 32, 64])
+@pytest.mark.parametrize("sink", [4, 33, 100])
+@pytest.mark.parametrize("H,meta,cb", [(16, "fp16", 4), (32, "paper", 2), (128, "fp16", 4)])
+def test_new_token_below_a_sink_without_window(H, meta, cb, sink, split):
+    """One new token on each side of the sink and no recent window (length
+    sink + 1, two query tokens): the packed tile of the one past the sink also
+    spans the slot of the one below it, which is written with the protected
+    rows by another wave or work item.  Every byte the step has not written is
+    0xFF (NaN scales), so an output that took anything from an unwritten slot
+    is NaN."""
+    import torch
+
+    from gpu_support import AttnStats, check_sequence_protected
+    from paper_2609_36760_amd import _binding as mb
+    from paper_2609_36760_amd.runner import DecodeRun
+    lens = np.full(6, sink + 1, np.int32)
+    w = syn.Workload("below_sink", 190 + sink + H, B=len(lens), H=H, s_q=2, context=None, layers=((cb, 4),),
+                     split_tokens=split, ctx_range=(1, 2))
+    run = DecodeRun(w, protect=mb.protect_policy(sink, 0), seq_lens=lens, meta=meta)
+    for _ in range(4):
+        run.cache.fill_(0xFF)
+        run._prefill(4)
+        run.fused_step()
+        torch.cuda.synchronize()
+        stats = AttnStats()
+        for b in range(len(lens)):
+            check_sequence_protected(stats, run, b)
+        stats.check(f"sink {sink}, split {split}, {H} heads")
+
+
 def test_timing_hook_leaves_outputs_and_times_the_kernel():
     """Events attached to the decode dispatch by mla_time_next_decode_launch:
     the outputs are unchanged, the pair is consumed by the decode dispatch (a
