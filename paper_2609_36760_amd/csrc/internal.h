@@ -160,6 +160,18 @@ constexpr int narrow_waves(int64_t blocks) { return blocks <= kCus ? 4 : blocks 
 //   272 items of 64           25.2 /  21.9 /  33.6 (the 64-row ones in two rounds)
 //   272 items of 2 048       269.9 / 198.5 / 188.5
 struct ShapeCost { float fixed, per_tile; };
+// Tokens per work item that an unsplit launch is taken to have.  Its lengths are
+// on the device, and the page table's width says little about them (a table is
+// padded to its longest sequence, or to the longest one that may come); a width
+// in the rule would also let the padding choose the order of a sequence's sums.
+// By the cost below, over up to 96 sequences of 192 to 512 tokens the shape for
+// 2 048 is at most 10 % from the best one (0.3 % on average), and over any
+// number of any length at most 5 % from the 64- or 128-row one; the shape for
+// 512 tokens is up to 35 % from that one on long sequences.  Measured at 8 to
+// 256 sequences of 200, 330 and 512 tokens, the shape for their own length is
+// the faster only at 200, in 4 of 40 launches (64 heads, 96 x 200: 17.3 us
+// against 19.3).
+constexpr int64_t kUnsplitTokens = 2048;
 inline RowShape choose_shape(bool lowbit, int64_t rows, int64_t num_work, int64_t tokens) {
     // [16 rows, 32 rows][4, 2, 1 waves], then 64 and 128 rows
     static constexpr ShapeCost kNarrowLowbit[2][3] = {{{12.0f, 0.62f}, {13.5f, 1.07f}, {14.8f, 2.08f}},

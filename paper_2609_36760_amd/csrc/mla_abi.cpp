@@ -254,8 +254,8 @@ int decode_common(const mla_cache_format* f, bool lowbit, const uint16_t* q_lat,
     const mla::CacheKind kind = !lowbit ? mla::KIND_BF16
                                 : f->c_bits == 4 ? (paper ? mla::KIND_C4R4P : mla::KIND_C4R4)
                                                  : (paper ? mla::KIND_C2R4P : mla::KIND_C2R4);
-    const int64_t most = split_tokens != 0 ? split_tokens : static_cast<int64_t>(max_pages_per_seq) * f->page_size;
-    a.shape = mla::choose_shape(lowbit, static_cast<int64_t>(s_q) * H, a.num_work, most);
+    a.shape = mla::choose_shape(lowbit, static_cast<int64_t>(s_q) * H, a.num_work,
+                                split_tokens != 0 ? split_tokens : mla::kUnsplitTokens);
     const bool narrow = s_q * H <= mla::kNarrowRows;
     if (nt != nullptr && B > 0) {
         // the workgroups that read a new token write it inside the decode launch

@@ -212,6 +212,19 @@ int main() {
                                    nullptr, nullptr, nullptr, nullptr) == MLA_OK);
         CHECK(g_last_kind == mla::KIND_BF16 && g_last_decode.g.page_bytes == 73728);
 
+        // the launch shape of an unsplit call does not depend on the page table's width
+        for (int heads : {32, 64, 128}) {
+            for (int batch : {2, 24, 64, 256, 544}) {
+                mla::DecodeArgs first{};
+                for (int width : {1, 8, 4096}) {
+                    CHECK(mla_lowbit_decode_attn(&f, ql, qr, cache, 4, bt, width, sl, batch, 1, heads, 0.1f, 0, nullptr,
+                                                 0, out, lse, nullptr, nullptr, nullptr, nullptr) == MLA_OK);
+                    if (width == 1) first = g_last_decode;
+                    CHECK(std::memcmp(&first.shape, &g_last_decode.shape, sizeof(first.shape)) == 0);
+                }
+            }
+        }
+
         // protected decode
         mla_protect_policy pol{4, 128};
         const void* prot = dev(21);
