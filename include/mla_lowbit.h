@@ -14,9 +14,10 @@
  *   - Pointers named as device buffers must be device memory of the current
  *     HIP device; host pointers are marked "host".  The caller owns every
  *     buffer; the library allocates nothing and keeps no state between calls
- *     except, per host thread, a copy of the last HIP error and the event
+ *     except, per host thread, a copy of the last HIP error, the event
  *     pair armed by mla_time_next_decode_launch (two handles, cleared by the
- *     decode dispatch that consumes them).
+ *     decode dispatch that consumes them) and, in tests, the launch shape set
+ *     for the next decode (csrc/internal.h).
  *   - bf16 tensors are passed as uint16_t bit patterns.  All tensors are dense
  *     and row-major in the index order given, unless a stride is an argument.
  *     Query, output and partial tensors must be 16-byte aligned (else

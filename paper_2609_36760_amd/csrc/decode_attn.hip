@@ -1435,17 +1435,22 @@ namespace {
 // tokens: 39.7, 56.1, 94.4 us against 42.8, 67.4, 114.1.
 template <int KIND, bool kProt>
 void launch_kind(const DecodeArgs& a, hipStream_t stream, const LaunchEvents& ev) {
-    const int64_t blocks = decode_workgroups(a.num_work, static_cast<int64_t>(a.s_q) * a.H, a.shape);
+    const int64_t blocks = decode_workgroups(a.num_work, static_cast<int64_t>(a.s_q) * a.H, a.shape.rows);
     const dim3 grid(static_cast<unsigned>(blocks)), block(kThreads);
-    if (a.shape == ROWS_64) dispatch_decode(decode_kernel<KIND, kProt, 2>, grid, block, stream, ev, a);
+    if (a.shape.rows == rows_per_block(2)) dispatch_decode(decode_kernel<KIND, kProt, 2>, grid, block, stream, ev, a);
     else dispatch_decode(decode_kernel<KIND, kProt, 1>, grid, block, stream, ev, a);
+}
+
+bool wide_shape(LaunchShape s) {
+    return s.waves == kWaves && (s.rows == rows_per_block(1) || s.rows == rows_per_block(2));
 }
 
 }  // namespace
 
 hipError_t launch_decode(CacheKind kind, const DecodeArgs& a, hipStream_t stream) {
     if (a.num_work == 0) return hipSuccess;
-    if (a.shape <= ROWS_32) return launch_decode_narrow(kind, a, stream);
+    if (a.shape.rows <= kNarrowRows) return launch_decode_narrow(kind, a, stream);
+    if (!wide_shape(a.shape)) return hipErrorInvalidValue;
     const LaunchEvents ev = take_launch_events();
     switch (kind) {
         case KIND_C4R4: launch_kind<KIND_C4R4, false>(a, stream, ev); break;
@@ -1459,7 +1464,8 @@ hipError_t launch_decode(CacheKind kind, const DecodeArgs& a, hipStream_t stream
 
 hipError_t launch_decode_protected(CacheKind kind, const DecodeArgs& a, hipStream_t stream) {
     if (a.num_work == 0) return hipSuccess;
-    if (a.shape <= ROWS_32) return launch_decode_narrow_protected(kind, a, stream);
+    if (a.shape.rows <= kNarrowRows) return launch_decode_narrow_protected(kind, a, stream);
+    if (!wide_shape(a.shape)) return hipErrorInvalidValue;
     const LaunchEvents ev = take_launch_events();
     switch (kind) {
         case KIND_C4R4: launch_kind<KIND_C4R4, true>(a, stream, ev); break;

@@ -1137,38 +1137,41 @@ void narrow_kernel(DecodeArgs a) {
 }
 
 template <int KIND, bool kProt, int kR>
-void launch_rows(const DecodeArgs& a, hipStream_t stream, const LaunchEvents& ev) {
-    const int64_t blocks = decode_workgroups(a.num_work, static_cast<int64_t>(a.s_q) * a.H, kR);
-    const dim3 grid(static_cast<unsigned>(blocks));
-    switch (narrow_waves(blocks)) {
-        case 4: dispatch_decode(narrow_kernel<KIND, kProt, kR, 4>, grid, dim3(256), stream, ev, a); break;
-        case 2: dispatch_decode(narrow_kernel<KIND, kProt, kR, 2>, grid, dim3(128), stream, ev, a); break;
-        default: dispatch_decode(narrow_kernel<KIND, kProt, kR, 1>, grid, dim3(64), stream, ev, a); break;
+bool launch_rows(const DecodeArgs& a, hipStream_t stream, const LaunchEvents& ev) {
+    const dim3 grid(static_cast<unsigned>(decode_workgroups(a.num_work, static_cast<int64_t>(a.s_q) * a.H, kR)));
+    switch (a.shape.waves) {
+        case 4: dispatch_decode(narrow_kernel<KIND, kProt, kR, 4>, grid, dim3(256), stream, ev, a); return true;
+        case 2: dispatch_decode(narrow_kernel<KIND, kProt, kR, 2>, grid, dim3(128), stream, ev, a); return true;
+        case 1: dispatch_decode(narrow_kernel<KIND, kProt, kR, 1>, grid, dim3(64), stream, ev, a); return true;
+        default: return false;
     }
 }
 
 template <int KIND, bool kProt>
-void launch_kind(const DecodeArgs& a, hipStream_t stream, const LaunchEvents& ev) {
-    if (a.shape == ROWS_16) launch_rows<KIND, kProt, 16>(a, stream, ev);
-    else launch_rows<KIND, kProt, kMaxRows>(a, stream, ev);
+bool launch_kind(const DecodeArgs& a, hipStream_t stream, const LaunchEvents& ev) {
+    switch (a.shape.rows) {
+        case 16: return launch_rows<KIND, kProt, 16>(a, stream, ev);
+        case 32: return launch_rows<KIND, kProt, 32>(a, stream, ev);
+        default: return false;
+    }
 }
 
 template <bool kProt>
 hipError_t launch(CacheKind kind, const DecodeArgs& a, hipStream_t stream) {
     if (a.num_work == 0) return hipSuccess;
     const LaunchEvents ev = take_launch_events();
-    static_assert(kNarrowThreads == 64 && kNarrowRowsPerBlock == 16, "the host checks the largest launch");
+    static_assert(kNarrowThreads == kWaveThreads && kNarrowRowsPerBlock == 16, "the host checks the largest launch");
+    bool ok = false;
     switch (kind) {
-        case KIND_C4R4: launch_kind<KIND_C4R4, kProt>(a, stream, ev); break;
-        case KIND_C2R4: launch_kind<KIND_C2R4, kProt>(a, stream, ev); break;
-        case KIND_C4R4P: launch_kind<KIND_C4R4P, kProt>(a, stream, ev); break;
-        case KIND_C2R4P: launch_kind<KIND_C2R4P, kProt>(a, stream, ev); break;
+        case KIND_C4R4: ok = launch_kind<KIND_C4R4, kProt>(a, stream, ev); break;
+        case KIND_C2R4: ok = launch_kind<KIND_C2R4, kProt>(a, stream, ev); break;
+        case KIND_C4R4P: ok = launch_kind<KIND_C4R4P, kProt>(a, stream, ev); break;
+        case KIND_C2R4P: ok = launch_kind<KIND_C2R4P, kProt>(a, stream, ev); break;
         case KIND_BF16:
-            if constexpr (kProt) return hipErrorInvalidValue;
-            else launch_kind<KIND_BF16, false>(a, stream, ev);
+            if constexpr (!kProt) ok = launch_kind<KIND_BF16, false>(a, stream, ev);
             break;
     }
-    return hipGetLastError();
+    return ok ? hipGetLastError() : hipErrorInvalidValue;
 }
 
 }  // namespace

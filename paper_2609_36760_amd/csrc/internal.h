@@ -2,6 +2,7 @@
 // Not part of the public C ABI.
 #pragma once
 
+#include <cmath>
 #include <cstdint>
 
 #include <hip/hip_runtime_api.h>
@@ -46,12 +47,15 @@ struct AppendArgs {
 // Low-bit kinds: content bits and metadata storage (P: the paper's record).
 enum CacheKind { KIND_C4R4 = 0, KIND_C2R4 = 1, KIND_BF16 = 2, KIND_C4R4P = 3, KIND_C2R4P = 4 };
 
-// Query rows of a workgroup: 16 or 32 (decode_narrow.hip, one to four waves on
-// one row block) or 64 or 128 (decode_attn.hip, four waves on one tile).
-enum RowShape { ROWS_16 = 16, ROWS_32 = 32, ROWS_64 = 64, ROWS_128 = 128 };
+// Query rows and waves of a workgroup: 16 or 32 rows (decode_narrow.hip: one,
+// two or four waves on one row block, each with its part of the keys), or 64 or
+// 128 (decode_attn.hip: four waves on one tile).
+struct LaunchShape {
+    int32_t rows, waves;
+};
 
 struct DecodeArgs {
-    RowShape shape;         // of the launch (choose_shape)
+    LaunchShape shape;      // of the launch (choose_shape)
     const uint16_t* q_lat;
     const uint16_t* q_rope;
     const uint8_t* cache;
@@ -105,21 +109,25 @@ LaunchEvents take_launch_events();
 
 hipError_t launch_lowbit_append(const AppendArgs& a, hipStream_t stream);
 hipError_t launch_bf16_append(const AppendArgs& a, hipStream_t stream);
-// (launch_decode hands launches of 16- and 32-row shape on to the narrow kernel)
+// Decode in a.shape.  launch_decode takes every shape (those of 16 and 32 rows it
+// hands on), launch_decode_narrow, for up to kNarrowRows query rows, those of 16
+// and 32 rows; a shape that neither kernel has is refused.
+constexpr int kNarrowRows = 32;
 hipError_t launch_decode(CacheKind kind, const DecodeArgs& a, hipStream_t stream);
 hipError_t launch_decode_protected(CacheKind kind, const DecodeArgs& a, hipStream_t stream);
-// The same computation in 16- or 32-row workgroups.
-constexpr int kNarrowRows = 32;
+hipError_t launch_decode_narrow(CacheKind kind, const DecodeArgs& a, hipStream_t stream);
+hipError_t launch_decode_narrow_protected(CacheKind kind, const DecodeArgs& a, hipStream_t stream);
 
 // Launch shapes, for the host's size checks (each kernel file asserts its own
 // constants against these).  A dispatch packet holds the launch's work-item
 // count in 32 bits, so a launch of more than kMaxDispatchItems work items
 // cannot be expressed: the host refuses such shapes before any HIP call.
 constexpr int64_t kMaxDispatchItems = 0xFFFFFFFFll;
+constexpr int kWaveThreads = 64;
 constexpr int kDecodeThreads = 256;          // decode_attn.hip: 4 waves per workgroup
-constexpr int kDecodeRowsPerBlock = 128;     // query rows per workgroup
-constexpr int kNarrowThreads = 64;           // decode_narrow.hip: one wave per workgroup
-constexpr int kNarrowRowsPerBlock = 16;
+constexpr int kDecodeRowsPerBlock = 128;     // query rows of its widest shape
+constexpr int kNarrowThreads = 64;           // decode_narrow.hip in its largest launch: one wave per workgroup
+constexpr int kNarrowRowsPerBlock = 16;      // of 16 rows
 constexpr int kWorkGroupRound = 8;           // work items padded to a multiple of the 8 XCDs
 constexpr int kCombineThreads = 256;         // combine.hip: at most one row per workgroup
 constexpr int kAppendThreadsPerToken = 72;   // quant_append.hip: 9 groups x 8 lanes
@@ -132,8 +140,6 @@ constexpr int64_t decode_workgroups(int64_t num_work, int64_t rows, int64_t rows
     return (num_work + kWorkGroupRound - 1) / kWorkGroupRound * kWorkGroupRound *
            ((rows + rows_per_block - 1) / rows_per_block);
 }
-hipError_t launch_decode_narrow(CacheKind kind, const DecodeArgs& a, hipStream_t stream);
-hipError_t launch_decode_narrow_protected(CacheKind kind, const DecodeArgs& a, hipStream_t stream);
 
 // Waves per 16- or 32-row workgroup: they share the work item's keys.  A
 // workgroup of w waves takes w of a compute unit's four SIMDs, so up to 256
@@ -172,41 +178,59 @@ struct ShapeCost { float fixed, per_tile; };
 // the faster only at 200, in 4 of 40 launches (64 heads, 96 x 200: 17.3 us
 // against 19.3).
 constexpr int64_t kUnsplitTokens = 2048;
-inline RowShape choose_shape(bool lowbit, int64_t rows, int64_t num_work, int64_t tokens) {
+inline LaunchShape choose_shape(bool lowbit, int64_t rows, int64_t num_work, int64_t tokens) {
     // [16 rows, 32 rows][4, 2, 1 waves], then 64 and 128 rows
     static constexpr ShapeCost kNarrowLowbit[2][3] = {{{12.0f, 0.62f}, {13.5f, 1.07f}, {14.8f, 2.08f}},
                                                       {{17.5f, 0.72f}, {18.5f, 1.45f}, {20.0f, 2.95f}}};
     static constexpr ShapeCost kNarrowBf16[2][3] = {{{11.5f, 0.82f}, {13.0f, 1.8f}, {15.5f, 3.4f}},
                                                     {{15.5f, 1.05f}, {18.5f, 2.2f}, {21.0f, 3.9f}}};
     static constexpr ShapeCost kWide[2][2] = {{{18.5f, 1.25f}, {17.5f, 1.6f}}, {{17.5f, 1.1f}, {17.5f, 1.4f}}};
-    if (rows <= ROWS_16) return ROWS_16;
-    RowShape best = ROWS_128;
-    float least = 0.0f;
+    if (rows <= 16) return {16, narrow_waves(decode_workgroups(num_work, rows, 16))};
+    LaunchShape best{32, 1};        // (up to 32 rows; replaced below in any case)
+    float least = HUGE_VALF;
     const float n = static_cast<float>((tokens + 31) / 32);
-    if (rows > ROWS_32) {
-        const bool half = rows <= ROWS_64;
+    if (rows > kNarrowRows) {
+        const bool half = rows <= 64;
         const ShapeCost c = kWide[lowbit ? 0 : 1][half ? 0 : 1];
-        best = half ? ROWS_64 : ROWS_128;
+        best = {half ? 64 : 128, 4};
         const int64_t blocks = decode_workgroups(num_work, rows, kDecodeRowsPerBlock);
         least = static_cast<float>((blocks + kCus - 1) / kCus) * (c.fixed + n * c.per_tile);
     }
     for (int i = 0; i < 2; ++i) {
-        const int64_t blocks = decode_workgroups(num_work, rows, i == 0 ? ROWS_16 : ROWS_32);
+        const int64_t blocks = decode_workgroups(num_work, rows, i == 0 ? 16 : 32);
         const int w = narrow_waves(blocks);
-        if (blocks * w * kNarrowThreads > kMaxDispatchItems) continue;      // (decode_fits checked the widest shape)
+        if (blocks * w * kWaveThreads > kMaxDispatchItems) continue;        // (the host checked the other shapes)
         // the bf16 weights of one-wave workgroups (decode_narrow.hip) are left to
         // launches of at most 32 rows
-        if (!lowbit && w == 1 && rows > ROWS_32) continue;
+        if (!lowbit && w == 1 && rows > kNarrowRows) continue;
         const ShapeCost c = (lowbit ? kNarrowLowbit : kNarrowBf16)[i][w == 4 ? 0 : w == 2 ? 1 : 2];
         const float rounds = static_cast<float>((blocks * w + 4 * kCus - 1) / (4 * kCus));
         const float cost = rounds * (c.fixed + n * c.per_tile);
-        if (least == 0.0f || cost < least) {
+        if (cost < least) {
             least = cost;
-            best = i == 0 ? ROWS_16 : ROWS_32;
+            best = {i == 0 ? 16 : 32, w};
         }
     }
     return best;
 }
+// Whether a decode of `rows` query rows may run in shape s: one that choose_shape
+// gives to some launch of that many rows, and that fits one dispatch.
+inline bool shape_allowed(bool lowbit, int64_t rows, int64_t num_work, LaunchShape s) {
+    if (decode_workgroups(num_work, rows, s.rows > 0 ? s.rows : 1) * s.waves * kWaveThreads > kMaxDispatchItems) return false;
+    if (s.rows == 64) return s.waves == 4 && rows > kNarrowRows && rows <= 64;
+    if (s.rows == 128) return s.waves == 4 && rows > 64;
+    if (s.rows != 16 && !(s.rows == 32 && rows > 16)) return false;
+    return s.waves == 4 || s.waves == 2 || (s.waves == 1 && (lowbit || rows <= kNarrowRows));
+}
+
+// For tests and measurements of one shape (exported, not part of the public ABI).
+// mla_internal_decode_shape: the shape a decode call runs in, 8 * rows + waves
+// (split_tokens = 0: unsplit).  mla_internal_shape_next_decode: the calling
+// thread's next decode call that launches runs in this shape, or returns
+// MLA_EINVAL if the shape is not one for its rows; one-shot, 0 and 0 clear it.
+extern "C" int32_t mla_internal_decode_shape(int32_t lowbit, int32_t rows, int32_t num_work, int32_t split_tokens);
+extern "C" void mla_internal_shape_next_decode(int32_t rows, int32_t waves);
+
 hipError_t launch_lowbit_append_protected(const AppendArgs& a, hipStream_t stream);
 // num_splits (split_indptr[B]) chooses between one wave per row and four waves sharing a row.
 hipError_t launch_combine(const CombineArgs& a, int32_t num_splits, hipStream_t stream);

@@ -14,6 +14,7 @@ namespace {
 
 thread_local int g_last_hip_error = 0;
 thread_local mla::LaunchEvents g_launch_events{nullptr, nullptr};
+thread_local mla::LaunchShape g_next_shape{0, 0};       // mla_internal_shape_next_decode
 
 constexpr int32_t kDc = 512;
 constexpr int32_t kDr = 64;
@@ -165,8 +166,10 @@ struct NewTokens {
 };
 
 // Whether the decode launch over num_work work items fits one dispatch (its
-// work-item count is 32 bits): the wide kernel's 256-thread workgroups of 128
-// rows, or the 16-row kernel's one-wave workgroups when s_q * H <= 32.
+// work-item count is 32 bits) in the shape that a large launch takes: four-wave
+// workgroups of 128 rows (of 64 rows, one per work item as well), or one-wave
+// workgroups of 16 rows when s_q * H <= 32.  choose_shape passes over the other
+// shapes where they would not fit.
 bool decode_fits(int64_t num_work, int32_t s_q, int32_t H) {
     const int64_t rows = static_cast<int64_t>(s_q) * H;
     const bool narrow = rows <= mla::kNarrowRows;
@@ -256,6 +259,11 @@ int decode_common(const mla_cache_format* f, bool lowbit, const uint16_t* q_lat,
                                                  : (paper ? mla::KIND_C2R4P : mla::KIND_C2R4);
     a.shape = mla::choose_shape(lowbit, static_cast<int64_t>(s_q) * H, a.num_work,
                                 split_tokens != 0 ? split_tokens : mla::kUnsplitTokens);
+    if (g_next_shape.rows != 0 && a.num_work != 0) {
+        a.shape = g_next_shape;
+        g_next_shape = {0, 0};
+        if (!mla::shape_allowed(lowbit, static_cast<int64_t>(s_q) * H, a.num_work, a.shape)) return MLA_EINVAL;
+    }
     const bool narrow = s_q * H <= mla::kNarrowRows;
     if (nt != nullptr && B > 0) {
         // the workgroups that read a new token write it inside the decode launch
@@ -284,6 +292,13 @@ LaunchEvents take_launch_events() {
     g_launch_events = LaunchEvents{nullptr, nullptr};
     return e;
 }
+
+extern "C" int32_t mla_internal_decode_shape(int32_t lowbit, int32_t rows, int32_t num_work, int32_t split_tokens) {
+    const LaunchShape s = choose_shape(lowbit != 0, rows, num_work, split_tokens != 0 ? split_tokens : kUnsplitTokens);
+    return 8 * s.rows + s.waves;
+}
+
+extern "C" void mla_internal_shape_next_decode(int32_t rows, int32_t waves) { g_next_shape = {rows, waves}; }
 }  // namespace mla
 
 // Append the step's new tokens, then decode (one launch for the wide kernel).
