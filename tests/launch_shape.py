@@ -8,6 +8,7 @@ one, two or four waves that share a work item's keys (decode_narrow.hip), 64 or
 from __future__ import annotations
 
 import contextlib
+import inspect
 
 NARROW = [(16, 1), (16, 2), (16, 4), (32, 1), (32, 2), (32, 4)]
 
@@ -35,38 +36,50 @@ def set_next(shape: tuple[int, int]) -> None:
     mb.library().mla_internal_shape_next_decode(*shape)
 
 
+DECODE_CALLS = ("mla_lowbit_decode_attn", "mla_bf16_decode_attn", "mla_lowbit_append_decode_attn",
+                "mla_bf16_append_decode_attn", "mla_lowbit_decode_attn_protected",
+                "mla_lowbit_append_decode_attn_protected", "mla_lowbit_decode_attn_noalloc")
+
+
 @contextlib.contextmanager
 def pinned(shape):
-    """Every decode call of a DecodeRun inside the block runs in ``shape`` (None:
-    in the shape the library chooses)."""
-    from paper_2609_36760_amd.runner import DecodeRun
+    """Every decode call of the binding inside the block runs in ``shape``: a
+    pair, "wide" for :func:`wide` of the call's rows (calls of up to 32 rows run
+    as they would), or None for the shape the library chooses."""
+    from paper_2609_36760_amd import _binding as mb
     if shape is None:
         yield
         return
-    calls = {n: getattr(DecodeRun, n) for n in ("attend", "fused_step")}
+    calls = {n: getattr(mb, n) for n in DECODE_CALLS}
 
     def wrapped(call):
-        def run(self, *args, **kw):
-            set_next(shape)
-            return call(self, *args, **kw)
+        sig = inspect.signature(call)
+
+        def run(*args, **kw):
+            given = sig.bind(*args, **kw).arguments
+            rows = given["s_q"] * given["H"]
+            if shape != "wide":
+                set_next(shape)
+            elif rows > 32:
+                set_next(wide(rows))
+            return call(*args, **kw)
         return run
 
     for n, call in calls.items():
-        setattr(DecodeRun, n, wrapped(call))
+        setattr(mb, n, wrapped(call))
     try:
         yield
     finally:
         for n, call in calls.items():
-            setattr(DecodeRun, n, call)
+            setattr(mb, n, call)
         set_next((0, 0))
 
 
 def with_wide(cases, rows_of):
-    """(case, shape) pairs: every case in the shape the library chooses for it
-    (few work items: 16 or 32 rows), and those of more than 32 query rows in the
-    64- or 128-row one of large launches too."""
-    return [(c, None) for c in cases] + [(c, wide(rows_of(c))) for c in cases if rows_of(c) > 32]
-
-
-def ids(pairs, name_of=lambda c: c[0]):
-    return [name_of(c) + ("" if s is None else f"-rows{s[0]}") for c, s in pairs]
+    """Parameters (case, launch_shape): every case in the shape the library
+    chooses for it -- small tests have few work items, which run in 16- or 32-row
+    workgroups -- and those of more than 32 query rows (``rows_of(case)``) in the
+    64- or 128-row workgroups of large launches as well."""
+    import pytest
+    return ([pytest.param(c, None, id=c[0]) for c in cases] +
+            [pytest.param(c, "wide", id=f"{c[0]}-wide") for c in cases if rows_of(c) > 32])

@@ -145,7 +145,8 @@ def make_inputs(mode: str, lens, s_q: int, H: int, split_tokens: int, seed: int,
 
 # The structured GPU cases: (name, kind, c_bits, meta, H, s_q, split_tokens,
 # protect (sink, recent) or None, lens).  Lengths sit on and around tile, page
-# and split edges; 16 and 32 heads run the narrow kernel.
+# and split edges; few work items: they run in 16-row
+# workgroups, and from 33 rows in 128-row ones when a test asks for those.
 CASES = [
     ("c4_h128_sq1_nosplit", "lowbit", 4, "fp16", 128, 1, 0, None, [1, 31, 32, 33, 64, 65, 97, 200, 517]),
     ("c4_h128_sq2_split64", "lowbit", 4, "fp16", 128, 2, 64, None, [2, 33, 64, 65, 66, 129, 300]),

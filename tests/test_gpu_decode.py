@@ -4,7 +4,9 @@ Small cases compare every output of every row with the oracle (exact softmax
 in fp64 over the oracle's own reconstruction of the same cache); they span
 several tiles, ragged tails, one- and two-token queries, split and unsplit
 launches, 4-bit and 2-bit content, the BF16 cache and 16 to 512 query rows
-(one to four 128-row blocks per work item, the last one part-filled).
+(one to four 128-row blocks per work item, the last one part-filled).  These
+few work items run in 16-row workgroups; the cases of more than 32 rows run
+again in the 64- and 128-row workgroups of large launches.
 The full-size workloads run in the launch configuration the benchmark times
 and are compared on sampled sequences and heads.
 """
@@ -12,6 +14,7 @@ import numpy as np
 import pytest
 
 from gpu_support import FP16_LIMITED, AttnStats, bf16_bits_to_f64, check_fp16_limited, check_sequence, lse_bound
+from launch_shape import with_wide
 from oracle import attention as at
 from paper_2609_36760_amd import synthetic as syn
 
@@ -52,8 +55,8 @@ SMALL = [
 ]
 
 
-@pytest.mark.parametrize("case", SMALL, ids=[c[0] for c in SMALL])
-def test_decode_small_all_rows(case):
+@pytest.mark.parametrize("case,launch_shape", with_wide(SMALL, lambda c: c[1] * c[2]), indirect=["launch_shape"])
+def test_decode_small_all_rows(case, launch_shape):
     name, H, s_q, lens, cb, split = case
     kind = "bf16" if cb == "bf16" else "lowbit"
     bits = 4 if cb == "bf16" else cb
@@ -70,7 +73,8 @@ def test_decode_small_all_rows(case):
         stats.check(name)
 
 
-def test_split_partials_match_oracle_chunks():
+@pytest.mark.parametrize("launch_shape", [None, "wide", (32, 4)], indirect=True)
+def test_split_partials_match_oracle_chunks(launch_shape):
     """The partials themselves (before the combine) follow the chunk definition."""
     import torch
     w = syn.Workload("partials", 140, B=2, H=128, s_q=2, context=None, split_tokens=64, ctx_range=(1, 2))
@@ -124,7 +128,8 @@ def test_split_partials_match_oracle_chunks():
             assert np.all(np.abs(go[live] - want) <= tol)
 
 
-def test_large_score_jump_rescale():
+@pytest.mark.parametrize("launch_shape", [None, "wide", (16, 1), (32, 1), (32, 4)], indirect=True)
+def test_large_score_jump_rescale(launch_shape):
     """Scores that jump far above the first tiles' maximum: the running reference
     is raised and the accumulators rescaled in place."""
     import torch
@@ -174,7 +179,8 @@ def test_large_score_jump_rescale():
     stats.check("rescale")
 
 
-def test_identical_keys_give_the_key():
+@pytest.mark.parametrize("launch_shape", [None, "wide"], indirect=True)
+def test_identical_keys_give_the_key(launch_shape):
     import torch
 
     from paper_2609_36760_amd import _binding as mb

@@ -2,8 +2,8 @@
 
 The low-bit decode kernels reconstruct the cache in fp16 and run fp16
 products (the header's precondition: queries and dequantized latents within
-the fp16 range).  Pinned here, on the 128-head and 16-head kernels, split and
-unsplit, with all-zero queries (every visible key weighs the same, Sec. 2.1,
+the fp16 range).  Pinned here, with 128 heads (in 16- and 128-row workgroups)
+and 16, split and unsplit, with all-zero queries (every visible key weighs the same, Sec. 2.1,
 eq. mla_compact):
 
   * at the edge: latents whose dequantized values reach about 5.9e4 in
@@ -24,6 +24,7 @@ import numpy as np
 import pytest
 
 from gpu_support import AttnStats, bf16_bits_to_f64, cache_values, compare_sequence, elem_bound, lse_bound
+from launch_shape import with_wide
 from oracle import attention as at
 from paper_2609_36760_amd import synthetic as syn
 
@@ -53,8 +54,8 @@ CASES = [
 ]
 
 
-@pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
-def test_fp16_range_edge_and_overflow(case):
+@pytest.mark.parametrize("case,launch_shape", with_wide(CASES, lambda c: 2 * c[1]), indirect=["launch_shape"])
+def test_fp16_range_edge_and_overflow(case, launch_shape):
     import torch
 
     from paper_2609_36760_amd.runner import DecodeRun

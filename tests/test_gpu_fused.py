@@ -6,14 +6,17 @@ mla_lowbit_decode_attn after it (+ the combine): the writer inside the decode
 launch runs the same quantizer, and the decode reads the same bytes.  Cases
 cover new tokens whose tile is staged in the prologue (short key ranges) and
 later (long ranges), a split boundary between the two new tokens of a
-sequence, two row blocks per work item (s_q = 2, 128 heads: both write the
-same bytes; four at 256 heads, and a part-filled second one at 80), 4-bit,
-2-bit and BF16 caches, the paper's metadata, and the 16-row kernel (16 and 32
-rows; s_q = 2 at 16 heads: two row blocks).
+sequence, two 128-row blocks per work item (s_q = 2, 128 heads: both write
+the same bytes; four at 256 heads, and a part-filled second one at 80), 4-bit,
+2-bit and BF16 caches, the paper's metadata, and 16 and 32 rows.  Every case
+runs in the shape the library chooses (so few work items: 16-row workgroups,
+up to 32 row blocks of them), those of more than 32 rows in 64- and 128-row
+workgroups too.
 """
 import numpy as np
 import pytest
 
+from launch_shape import with_wide
 from paper_2609_36760_amd import synthetic as syn
 
 pytestmark = pytest.mark.gpu
@@ -41,8 +44,8 @@ CASES = [
 ]
 
 
-@pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
-def test_append_decode_matches_separate_calls(case):
+@pytest.mark.parametrize("case,launch_shape", with_wide(CASES, lambda c: c[1] * c[2]), indirect=["launch_shape"])
+def test_append_decode_matches_separate_calls(case, launch_shape):
     import torch
 
     from paper_2609_36760_amd.runner import DecodeRun
@@ -79,16 +82,17 @@ PROTECTED = [
 ]
 
 
-@pytest.mark.parametrize("case", PROTECTED, ids=[c[0] for c in PROTECTED])
-def test_protected_append_decode_matches_separate_calls(case):
+@pytest.mark.parametrize("case,launch_shape", with_wide(PROTECTED, lambda c: c[3] * c[4]), indirect=["launch_shape"])
+def test_protected_append_decode_matches_separate_calls(case, launch_shape):
     """mla_lowbit_append_decode_attn_protected against the protected writer
     followed by the protected decode, over consecutive steps across the
     window's edge: identical packed pages, protection buffers, outputs and
     lse after every step.  Cases: new tokens in a work item's first staged
     tiles and later, sequences still entirely protected, a protected phase
-    that starts a work item, two row blocks (s_q = 2 at 128 heads), a one-row
-    window (the older new token read packed), sink rows only, INT2, the
-    paper's metadata, and the 16-row kernel (16 and 32 rows)."""
+    that starts a work item, two 128-row blocks (s_q = 2 at 128 heads), a
+    one-row window (the older new token read packed), sink rows only, INT2, the
+    paper's metadata, 16 and 32 rows; 16-row workgroups, and from 33 rows 64-
+    and 128-row ones too."""
     import torch
 
     from paper_2609_36760_amd import _binding as mb
@@ -123,8 +127,10 @@ def test_protected_append_decode_matches_separate_calls(case):
 
 @pytest.mark.parametrize("split", [0, 32, 64])
 @pytest.mark.parametrize("sink", [4, 33, 100])
-@pytest.mark.parametrize("H,meta,cb", [(16, "fp16", 4), (32, "paper", 2), (128, "fp16", 4)])
-def test_new_token_below_a_sink_without_window(H, meta, cb, sink, split):
+@pytest.mark.parametrize("H,meta,cb,launch_shape", [(16, "fp16", 4, None), (32, "paper", 2, None), (32, "fp16", 2, "wide"),
+                                                    (128, "fp16", 4, None), (128, "paper", 4, "wide")],
+                         indirect=["launch_shape"])
+def test_new_token_below_a_sink_without_window(H, meta, cb, sink, split, launch_shape):
     """One new token on each side of the sink and no recent window (length
     sink + 1, two query tokens): the packed tile of the one past the sink also
     spans the slot of the one below it, which is written with the protected

@@ -8,14 +8,15 @@ and protection bytes it writes) kept, the outputs poisoned, the step captured,
 and the graph replayed three times with unrelated eager work and a
 synchronization between replays; after every replay the outputs, lse, cache
 and protection buffers must equal the eager ones bit for bit.  The steps: the
-append inside the decode launch, then the combine (128-row and 16-row kernels,
-INT4 and BF16 caches, BF16 protection); the writer, decode and combine as
+append inside the decode launch, then the combine (16-row workgroups, and for
+128 and 256 rows 128-row ones too; INT4 and BF16 caches, BF16 protection); the writer, decode and combine as
 three calls; and the allocation-free entry point (its partials in the
 library's static storage).
 """
 import numpy as np
 import pytest
 
+from launch_shape import with_wide
 from paper_2609_36760_amd import synthetic as syn
 
 pytestmark = pytest.mark.gpu
@@ -32,8 +33,8 @@ CASES = [
 ]
 
 
-@pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
-def test_graph_replay_matches_eager(case):
+@pytest.mark.parametrize("case,launch_shape", with_wide(CASES, lambda c: c[1] * c[2]), indirect=["launch_shape"])
+def test_graph_replay_matches_eager(case, launch_shape):
     import torch
 
     from paper_2609_36760_amd import _binding as mb

@@ -6,7 +6,7 @@ The library takes any page size that is a multiple of 32 tokens (at most
 kernel half of one), 96 (not a power of two: tiles start at offsets 0, 32 and
 64 of a page in turn, and key splits of 192 tokens end mid-page), 128 and 1024
 tokens, through the writer, the decode launch and the step with the append
-inside it, for the 128-row and 16-row kernels, INT4, INT2, the BF16 cache,
+inside it, in 16-row and (from 128 rows) 128-row workgroups, INT4, INT2, the BF16 cache,
 the paper's metadata record and BF16 protection of sink and recent tokens.
 Each sequence's pages are read back and compared byte for byte with the
 oracle's packing at the same page size (Appendix C.4; Appendix C.5, "Storage
@@ -18,6 +18,7 @@ import numpy as np
 import pytest
 
 from gpu_support import AttnStats, check_sequence, check_sequence_protected
+from launch_shape import with_wide
 from paper_2609_36760_amd import synthetic as syn
 
 pytestmark = pytest.mark.gpu
@@ -45,8 +46,8 @@ def workload(case):
                         layers=((bits, 4),), split_tokens=split, ctx_range=(1, 2))
 
 
-@pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
-def test_decode_page_size_all_rows(case):
+@pytest.mark.parametrize("case,launch_shape", with_wide(CASES, lambda c: c[1] * c[2]), indirect=["launch_shape"])
+def test_decode_page_size_all_rows(case, launch_shape):
     import torch
 
     from paper_2609_36760_amd import _binding as mb

@@ -3,7 +3,8 @@ fp32 RoPE scales, byte zero-points; 320 B per token) against the oracle.
 
 The writer's bytes are covered bit-exactly in ``test_gpu_writer.py``; here
 every output of small ragged batches (4- and 2-bit content, one and two query
-tokens, split and unsplit, with and without BF16 protection) and sampled
+tokens, split and unsplit, with and without BF16 protection; 16-row workgroups, and
+64- and 128-row ones for as many rows) and sampled
 sequences of the 32 x 4096 benchmark shape are compared with the oracle's
 exact attention over its own reconstruction from the same stored scales,
 within the bounds of ``gpu_support``.
@@ -12,6 +13,7 @@ import numpy as np
 import pytest
 
 from gpu_support import AttnStats, check_sequence, check_sequence_protected
+from launch_shape import with_wide
 from paper_2609_36760_amd import synthetic as syn
 
 pytestmark = pytest.mark.gpu
@@ -38,8 +40,8 @@ SMALL = [
 ]
 
 
-@pytest.mark.parametrize("case", SMALL, ids=[c[0] for c in SMALL])
-def test_paper_format_decode_small_all_rows(case):
+@pytest.mark.parametrize("case,launch_shape", with_wide(SMALL, lambda c: c[1] * c[2]), indirect=["launch_shape"])
+def test_paper_format_decode_small_all_rows(case, launch_shape):
     from paper_2609_36760_amd import _binding as mb
     name, H, s_q, cb, split, prot, lens = case
     w = syn.Workload(name, 400 + SMALL.index(case), B=len(lens), H=H, s_q=s_q, context=None,

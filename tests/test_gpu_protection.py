@@ -11,13 +11,15 @@ boundary of the policy -- every token protected, the sink/window overlap, the
 first packed token, tile and split edges -- for one and two query tokens,
 split and unsplit launches, 4- and 2-bit content and several policies, checked
 against the oracle's single softmax over the per-token representations with
-the bounds of ``gpu_support``; the benchmark shape with the paper's policy on
+the bounds of ``gpu_support`` (16-row workgroups, and from 33 rows 64- and
+128-row ones too); the benchmark shape with the paper's policy on
 sampled sequences.
 """
 import numpy as np
 import pytest
 
 from gpu_support import FP16_LIMITED, AttnStats, check_fp16_limited, check_sequence_protected
+from launch_shape import with_wide
 from oracle import protection as pr
 from paper_2609_36760_amd import synthetic as syn
 
@@ -85,8 +87,8 @@ SMALL = [
 ]
 
 
-@pytest.mark.parametrize("case", SMALL, ids=[c[0] for c in SMALL])
-def test_protected_decode_small_all_rows(case):
+@pytest.mark.parametrize("case,launch_shape", with_wide(SMALL, lambda c: c[1] * c[2]), indirect=["launch_shape"])
+def test_protected_decode_small_all_rows(case, launch_shape):
     from paper_2609_36760_amd import _binding as mb
     name, H, s_q, cb, split, (sink, recent), lens = case
     w = syn.Workload(name, 310 + SMALL.index(case), B=len(lens), H=H, s_q=s_q, context=None,
@@ -155,8 +157,8 @@ AGING = [
 ]
 
 
-@pytest.mark.parametrize("case", AGING, ids=[c[0] for c in AGING])
-def test_token_aging_over_consecutive_steps(case):
+@pytest.mark.parametrize("case,launch_shape", with_wide(AGING, lambda c: c[2] * c[3]), indirect=["launch_shape"])
+def test_token_aging_over_consecutive_steps(case, launch_shape):
     """Consecutive decode steps of sequences that grow across the recent
     window's edge (Appendix C.5, "BF16 protection and cache lifecycle"): each
     step appends s_q tokens through the protected writer (the token entering

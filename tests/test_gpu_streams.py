@@ -5,7 +5,8 @@ last HIP error and an armed timing-event pair, and the allocation-free entry
 point's static storage, whose calls on one GPU must not overlap), so two steps
 on different buffers may run concurrently on two streams.  Each step's outputs,
 lse, cache and protection bytes after five interleaved launches on two streams
-must equal those of the same steps run one after the other on one stream.
+must equal those of the same steps run one after the other on one stream; the
+256-row step in the shape the library chooses and in 128-row workgroups.
 """
 import numpy as np
 import pytest
@@ -15,7 +16,8 @@ from paper_2609_36760_amd import synthetic as syn
 pytestmark = pytest.mark.gpu
 
 
-def test_two_streams_match_sequential_steps():
+@pytest.mark.parametrize("launch_shape", [None, "wide"], indirect=True)
+def test_two_streams_match_sequential_steps(launch_shape):
     import torch
 
     from paper_2609_36760_amd import _binding as mb

@@ -8,9 +8,10 @@ page, split, causal and protection edge.  A key dropped, counted twice, or
 scored from its neighbour fails these cases
 (``test_parity_sensitivity.py`` shows it on the CPU for every edge position).
 
-Covered: the wide kernel (128 heads; INT4, INT2, the paper's metadata, BF16,
-BF16 protection; one and two query tokens; split and unsplit) and the narrow
-kernel (16 and 32 heads; INT4, INT2, BF16, protection).  The uniform mode
+Covered: 128 heads in 128-row workgroups and, as the library shapes launches
+of so few work items, in 16-row ones (INT4, INT2, the paper's metadata, BF16,
+BF16 protection; one and two query tokens; split and unsplit), and 16 and 32
+heads (INT4, INT2, BF16, protection).  The uniform mode
 runs the separate writer launch, the needle mode (unprotected) the
 append-and-decode call the benchmark times.
 """
@@ -19,14 +20,15 @@ import pytest
 
 import structured as st
 from gpu_support import AttnStats, check_sequence, check_sequence_protected
+from launch_shape import with_wide
 from paper_2609_36760_amd import synthetic as syn
 
 pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("mode", ["uniform", "needle"])
-@pytest.mark.parametrize("case", st.CASES, ids=[c[0] for c in st.CASES])
-def test_structured_all_rows(case, mode):
+@pytest.mark.parametrize("case,launch_shape", with_wide(st.CASES, lambda c: c[4] * c[5]), indirect=["launch_shape"])
+def test_structured_all_rows(case, launch_shape, mode):
     import torch
 
     from paper_2609_36760_amd import _binding as mb

@@ -6,7 +6,8 @@ per-GPU storage and runs the combine itself; its outputs must equal, bit for
 bit, those of mla_lowbit_decode_attn into caller-owned partials followed by
 mla_splitkv_combine (the same kernels on the same inputs).  Two calls in a
 row, the second smaller, show that nothing of the first call's partials leaks
-into the second; unsplit and narrow (16-head) launches too.
+into the second; unsplit and 16-head launches too, and those of 128 and 256
+rows in 128-row workgroups as well as in the shape the library chooses.
 """
 import numpy as np
 import pytest
@@ -43,7 +44,8 @@ def _reference_and_noalloc(case):
     return run, out, lse
 
 
-def test_noalloc_matches_decode_and_combine_on_consecutive_calls():
+@pytest.mark.parametrize("launch_shape", [None, "wide"], indirect=True)
+def test_noalloc_matches_decode_and_combine_on_consecutive_calls(launch_shape):
     import torch
     for case in CALLS:
         run, out, lse = _reference_and_noalloc(case)
