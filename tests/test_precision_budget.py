@@ -271,6 +271,25 @@ def test_fp16_limited_batches_are_the_rounding_models():
     assert a_exact < 0.0125, a_exact
 
 
+def test_fp16_limited_batch_of_32_row_workgroups_is_the_rounding_models():
+    """The 128-head batch that test_gpu_row_regimes.py runs in 32-row workgroups
+    of two waves: the model's excess is the recorded one (the GPU measured
+    2.114e-2), and with exact content scores it is far below the rule."""
+    import test_gpu_row_regimes as rr
+    from gpu_support import FP16_LIMITED
+    name = "r128_two_waves"
+    case = next(c for c in rr.CASES if c[0] == name)
+    _, H, s_q, lens, cache, split, _, prot, compared, _ = case
+    assert (cache, split, prot) == ("c4", 0, None)
+    w = syn.Workload(name, 900 + rr.CASES.index(case), B=len(lens), H=H, s_q=s_q, context=None, layers=((4, 4),),
+                     split_tokens=split, ctx_range=(1, 2))
+    rows = _rows(w, [(b, lens[b]) for b in compared], np.arange(H))
+    _, _, r = _ratio(w, rows, _rnd_f16, _rnd_f16)
+    _, _, r_exact = _ratio(w, rows, _rnd_f16, _rnd_f16, score_round=_ident)
+    assert abs(r - FP16_LIMITED[name]) < 1e-4, r
+    assert r_exact < 0.01, r_exact
+
+
 def test_model_partials_combine_to_its_output():
     """The model's partials (the full-output GPU test compares the kernels'
     split partials with them) combine, exactly, to the model's unrounded
