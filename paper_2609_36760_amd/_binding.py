@@ -136,21 +136,30 @@ def _ptr(t):
         raise
 
 
-_torch = None
+_current_stream = None      # () -> raw handle of torch's current stream, once its HIP runtime is up
+
+
+def _stream_getter(torch):
+    """The handle asked for directly, on the current device, takes 0.2 us; building
+    a ``torch.cuda.Stream`` takes 2.8 (a whole append call took 7.2 us).  The
+    direct call is not part of torch's public interface: a torch without it
+    takes the public one."""
+    raw, device = (getattr(torch._C, n, None) for n in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))
+    if raw is None or device is None:
+        return lambda: torch.cuda.current_stream().cuda_stream
+    return lambda: raw(device())
 
 
 def _stream(stream):
-    """Raw handle of ``stream``, or of torch's current stream on the current
-    device: asked for directly, which takes 0.2 us where building a
-    ``torch.cuda.Stream`` takes 2.8 (a whole append call took 7.2 us)."""
-    global _torch
+    """Raw handle of ``stream``, or of torch's current stream on the current device."""
+    global _current_stream
     if stream is None:
-        if _torch is None:
+        if _current_stream is None:
             import torch
             if not torch.cuda.is_initialized():
                 return torch.cuda.current_stream().cuda_stream
-            _torch = torch
-        return _torch._C._cuda_getCurrentRawStream(_torch._C._cuda_getDevice())
+            _current_stream = _stream_getter(torch)
+        return _current_stream()
     return stream if isinstance(stream, int) else stream.cuda_stream
 
 
