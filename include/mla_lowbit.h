@@ -47,8 +47,9 @@
  *     not readable by the host without a synchronization and are preconditions:
  *     s_q <= seq_lens[b] <= max_pages_per_seq * page_size, 0 <= page id <
  *     num_pages, split_indptr as produced by mla_plan_splits, finite inputs.
- *     Kernels clamp every index into its buffer, so a violated precondition
- *     gives unspecified results but no out-of-bounds access.
+ *     The writers and decode kernels clamp every index into its buffer, so a
+ *     violated precondition gives unspecified results but no out-of-bounds
+ *     access; the combine reads the partials that split_indptr names.
  */
 #ifndef MLA_LOWBIT_H
 #define MLA_LOWBIT_H

@@ -862,7 +862,8 @@ void decode_kernel(DecodeArgs a) {
         // staging loads behind them.
         int pids[3] = {0, 0, 0};
         if constexpr (!kRing) {
-            auto pidx = [&](int j) { return (t_begin + (j < n_tiles ? j : 0) * kTile) / P; };
+            // (a range without keys may begin past the sequence's pages)
+            auto pidx = [&](int j) { return page_column(t_begin + (j < n_tiles ? j : 0) * kTile, P, a.max_pages); };
             issue_page_ids3(bt, pidx(0), pidx(1), pidx(2), pids[0], pids[1], pids[2]);
         }
         {
@@ -1268,7 +1269,7 @@ void decode_kernel(DecodeArgs a) {
         const int n_list = n_pk + (n_prot + kTile - 1) / kTile;
         int u0 = 0, u1 = n_list;
         if (a.split_tokens != 0) {
-            u0 = split * (a.split_tokens / kTile);
+            u0 = split_tile(split, a.split_tokens, n_list);
             u1 = min(u0 + a.split_tokens / kTile, n_list);
         }
         if constexpr (Cfg<KIND>::lowbit) {

@@ -964,7 +964,7 @@ void narrow_kernel(DecodeArgs a) {
         const int n_list = n_pk + (n_prot + 31) / 32;
         int u0 = 0, u1 = n_list;
         if (a.split_tokens != 0) {
-            u0 = split * (a.split_tokens / 32);
+            u0 = split_tile(split, a.split_tokens, n_list);
             u1 = min(u0 + a.split_tokens / 32, n_list);
         }
         part(u0, u1);

@@ -141,6 +141,18 @@ constexpr int64_t decode_workgroups(int64_t num_work, int64_t rows, int64_t rows
            ((rows + rows_per_block - 1) / rows_per_block);
 }
 
+// Indexes that come from device-resident values, kept inside their table for any
+// values (split_indptr not as planned, a plan for other lengths): the page-table
+// column of token t, and the first list tile of a split of a protected sequence.
+constexpr int32_t page_column(int32_t t, int32_t page_size, int32_t max_pages) {
+    const int32_t c = t / page_size;
+    return c < 0 ? 0 : c < max_pages ? c : max_pages - 1;
+}
+constexpr int32_t split_tile(int32_t split, int32_t split_tokens, int32_t n_list) {
+    const int64_t u = static_cast<int64_t>(split) * (split_tokens / 32);
+    return u < 0 ? 0 : u < n_list ? static_cast<int32_t>(u) : n_list;
+}
+
 // Waves per 16- or 32-row workgroup: they share the work item's keys.  A
 // workgroup of w waves takes w of a compute unit's four SIMDs, so up to 256
 // workgroups four waves cost nothing, up to 512 two; past that the extra waves

@@ -103,6 +103,27 @@ int main() {
     bad.d_c = -512;
     CHECK(mla_bf16_page_bytes(&bad) == -1);
 
+    // ---- indexes from device-resident values stay in their tables, also for a
+    // split plan of other lengths or no plan at all
+    for (int64_t t : {int64_t{0}, int64_t{63}, int64_t{64}, int64_t{255}, int64_t{256}, int64_t{1} << 30,
+                      int64_t{INT32_MAX}, int64_t{-1}, int64_t{INT32_MIN}}) {
+        for (int pages : {1, 4}) {
+            const int col = mla::page_column(static_cast<int32_t>(t), 64, pages);
+            CHECK(col >= 0 && col < pages);
+            if (t >= 0 && t < 64 * pages) CHECK(col == t / 64);
+        }
+    }
+    for (int32_t split : {0, 1, 3, 40, INT32_MAX, -1, INT32_MIN}) {
+        for (int32_t tokens : {32, 96, INT32_MAX - 31}) {
+            for (int n_list : {0, 1, 7, 1 << 26}) {
+                const int u = mla::split_tile(split, tokens, n_list);
+                CHECK(u >= 0 && u <= n_list);
+                const int64_t plain = int64_t{split} * (tokens / 32);
+                if (plain >= 0 && plain <= n_list) CHECK(u == plain);
+            }
+        }
+    }
+
     // ---- planners, including lengths near the int32 limit
     {
         const int32_t lens[4] = {1, 64, 65, 4096};
