@@ -220,8 +220,9 @@ int mla_lowbit_decode_attn(const mla_cache_format* f,
  * Same computation over a BF16 cache (the unquantized comparison; row layout
  * in mla_bf16_page_bytes).  Arguments as for mla_lowbit_decode_attn.  The
  * products run in bf16 (cache rows and queries exact), the softmax weights
- * rounded to bf16 (in launches of few work items to 16 significant bits).  With split partials, the cache values must lie within the
- * fp16 range (part_o is fp16).
+ * rounded to bf16, or in launches of few work items to 16 significant bits.
+ * With split partials, the cache values must lie within the fp16 range
+ * (part_o is fp16).
  */
 int mla_bf16_decode_attn(const mla_cache_format* f,
                          const uint16_t* q_lat, const uint16_t* q_rope,
@@ -244,8 +245,8 @@ int mla_bf16_decode_attn(const mla_cache_format* f,
  * is position seq_lens[b] - s_q + i of sequence b and is written at slot
  * slot_mapping[b * s_q + i] (device, int64; < 0 skips the token), which must
  * be that position's slot under block_table (a device-resident precondition).
- * The writer runs inside the decode launch: the workgroups that read a new
- * token's tile quantize and store it first.  Arguments and errors as for the
+ * The writer runs inside the decode launch: the workgroups (or their waves)
+ * that read a new token's tile quantize and store it first.  Arguments and errors as for the
  * two calls.
  */
 int mla_lowbit_append_decode_attn(const mla_cache_format* f,
@@ -368,8 +369,8 @@ int32_t mla_plan_splits_protected(const int32_t* seq_lens, int32_t B, int32_t sp
  * (prot_slot[b], clamped into [0, num_prot)) instead of the packed cache.
  * Split partials follow mla_plan_splits_protected; mla_splitkv_combine
  * merges them unchanged.  Products over protected rows run in bf16 (rows and
- * queries exact, weights rounded to bf16), over packed rows in fp16 as in
- * mla_lowbit_decode_attn.  Precondition: the buffer holds every position of
+ * queries exact, weights rounded to 16 significant bits), over packed rows in
+ * fp16 as in mla_lowbit_decode_attn.  Precondition: the buffer holds every position of
  * P_L (written by mla_lowbit_quant_append_protected).
  *   prot  device, num_prot protection buffers (16-byte aligned)
  */

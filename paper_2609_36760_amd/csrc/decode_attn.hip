@@ -13,7 +13,9 @@
 //
 // Workgroup = 4 waves = 256 threads, one per CU (one wave per SIMD); it owns
 // one (sequence or key split, block of 128 query rows); wave w owns rows
-// 32w..32w+31.
+// 32w..32w+31.  (Launches of 33 to 64 rows: 64 rows per workgroup, two waves on
+// each 32 of them; kernel part 3.  Launches of few work items run in the 16- or
+// 32-row workgroups of decode_narrow.hip.)
 //
 // Data path per 32-token tile:
 //   1. its packed bytes (code and metadata regions of the page) are copied
@@ -269,42 +271,6 @@ template <int N>
 __device__ __forceinline__ void plain_barrier() {
     static_assert(N >= 0 && N < 64, "vmcnt range");
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(N) : "memory");
-}
-
-// Packed tile: the content codes in whole rounds (chunk i of the region by
-// lane i % 64 of wave (i / 64) % 4), then one load per wave for the small
-// regions: wave 0 the RoPE codes, wave 1 the content metadata (or the paper's
-// 32-byte records), wave 2 the RoPE metadata, wave 3 the RoPE metadata again
-// into a spare area (every wave issues Cfg::loads loads; under the paper's
-// storage wave 2 too loads into the spare area).  Tokens at or past `nvalid` re-read token
-// nvalid - 1 (per-token regions; a RoPE metadata chunk holds four tokens and
-// is read as it is -- such a token's score is masked and its RoPE channels
-// never enter the aggregation).  Load `k` of the Cfg::loads.
-template <int KIND>
-__device__ __forceinline__ void stage_lowbit(int k, const uint8_t* page, int po, int nvalid, const PageGeom& g,
-                                             uint32_t st_lds, int wave, int wave_u, int lane) {
-    using C = Cfg<KIND>;
-    constexpr int cpt = C::cc / 16;                     // chunks per token
-    static_assert(C::code_rounds * kThreads * 16 == C::rcodes, "content codes fill whole rounds");
-    if (k < C::code_rounds) {
-        const int i = k * kThreads + wave * 64 + lane;
-        const int tok = min(i / cpt, nvalid - 1);
-        dma16(page, (po + tok) * C::cc + (i % cpt) * 16, st_lds + (k * kThreads + wave_u * 64) * 16);
-        return;
-    }
-    const int tok2 = min(lane >> 1, nvalid - 1);
-    int src_off, dst_off;
-    if (wave_u == 0) {
-        src_off = g.off_cr + (po + tok2) * 32 + (lane & 1) * 16;
-        dst_off = C::rcodes;
-    } else if (wave_u == 1) {
-        src_off = g.off_mc + (po + tok2) * 32 + (lane & 1) * 16;
-        dst_off = C::meta;
-    } else {
-        src_off = g.off_mr + po * 4 + (lane & 7) * 16;
-        dst_off = wave_u == 2 && !C::pmeta ? C::rmeta : C::spare;
-    }
-    if (wave_u < 2 || lane < 8) dma16(page, src_off, st_lds + dst_off);
 }
 
 // Raw bf16 rows into a tile of the plain layout (SC = 76): LDS chunk i of the
@@ -733,10 +699,15 @@ void decode_kernel(DecodeArgs a) {
         // Per-lane parts of the staging addresses, fixed for the whole run.
         // Packed: content chunk i of load k < code_rounds (i = 256 k + 64 wave +
         // lane) is chunk i % cpt of token i / cpt of the tile; a small region
-        // (RoPE codes, metadata) is read 16 bytes per lane from its start.  BF16
+        // (RoPE codes, metadata) is read 16 bytes per lane from its start: wave 0
+        // the RoPE codes, wave 1 the content metadata (or the paper's records), wave
+        // 2 the RoPE metadata, wave 3 (and wave 2 of the paper's storage) the same
+        // into a spare area, so that every wave issues Cfg::loads loads.  BF16
         // rows: row and column of the lane's chunk, two loads per register.
         // Tokens at or past the range's end re-read its last token (nvalid - 1),
-        // so the address is one clamp and one shift-add per load.
+        // so the address is one clamp and one shift-add per load.  (A RoPE metadata
+        // chunk holds four tokens and is read as it is: the score of a token past
+        // the end is masked and its RoPE channels never enter the aggregation.)
         constexpr int cpt = C::lowbit ? C::cc / 16 : 1;           // content chunks per token
         constexpr int kBfPairs = C::lowbit ? 1 : (C::loads + 1) / 2;
         uint32_t c_tok = 0, c_col = 0, s_tok = 0, s_col = 0;
@@ -1127,8 +1098,8 @@ void decode_kernel(DecodeArgs a) {
                     } else if constexpr (kPairW) {
                         l_run += p0 + p1;
                         pw[v2] = pack_bf16x2(p0, p1);
-                        // w - bf16(w) is exact in fp32 (|r| <= 2^-9 |w|); its bf16 rounding
-                        // leaves each weight to a relative 2^-17
+                        // w - bf16(w) is exact in fp32 (|r| <= 2^-8 |w|); its bf16 rounding
+                        // leaves each weight to a relative 2^-16
                         const float h0 = __uint_as_float(pw[v2] << 16), h1 = __uint_as_float(pw[v2] & 0xFFFF0000u);
                         pwl[v2 % (kPairW ? kPw : 1)] = pack_bf16x2(p0 - h0, p1 - h1);
                         asm volatile("" : "+v"(pwl[v2 % (kPairW ? kPw : 1)]));

@@ -242,15 +242,17 @@ __device__ __forceinline__ void zero_offsets(f16x2 zz, f16x2* zo) {
 
 // In-launch append (the writer of mla_lowbit_quant_append / mla_bf16_append,
 // and under protection of mla_lowbit_quant_append_protected, for the step's
-// new tokens), as in decode_attn.hip: the work item that reads a new token
-// (`reads(p)`: its key range, or under protection its key list, holds
-// position p) writes it before it stages any tile -- the packed copy (BF16:
+// new tokens), as in decode_attn.hip: the wave that reads a new token
+// (`reads(p)`: its part of the key range, or under protection of the key list,
+// holds position p; every row block writes the same bytes itself) writes it
+// before it loads any tile -- the packed copy (BF16:
 // the row), and under protection, for a token protected after the step, its
 // bf16 row into ring row p or sink + (p - sink) mod recent of the sequence's
 // buffer (skipped for a buffer index outside [0, num_prot)).  One 16-byte
 // piece per lane and round (72 per token; a group's 8 lanes stay together,
-// as the quantizer needs); the wave's stores land before its first staging
-// load.
+// as the quantizer needs); the wave's stores land before its first tile's
+// loads.  The token's bytes enter no other wave's products, masked or not (the
+// first tile leaves out the places below the sink).
 template <int KIND, bool kProt, class Reads>
 __device__ __forceinline__ void narrow_append(const DecodeArgs& a, int b, int L, Reads reads, int lane) {
     using C = NCfg<KIND>;

@@ -156,7 +156,14 @@ constexpr int32_t split_tile(int32_t split, int32_t split_tokens, int32_t n_list
 // Waves per 16- or 32-row workgroup: they share the work item's keys.  A
 // workgroup of w waves takes w of a compute unit's four SIMDs, so up to 256
 // workgroups four waves cost nothing, up to 512 two; past that the extra waves
-// only queue (16 rows, 520 work items of 64 tokens: 16.1, 22.3, 27.8 us at 1, 2, 4).
+// only queue.  16 rows, INT4, us at 1 / 2 / 4 waves:
+//                 64 tokens           256                  480                 1 024
+//   256 items  10.7 /  9.9 / 10.3  22.3 / 16.7 / 14.9  35.7 / 24.4 / 19.9  68.2 / 41.0 / 28.4
+//   264        11.3 / 11.9 / 18.4  23.5 / 18.4 / 26.6  37.4 / 26.1 / 34.5  71.5 / 42.3 / 51.2
+//   512        13.1 / 13.6 / 20.5  26.1 / 20.6 / 30.3  39.8 / 28.9 / 39.4  74.5 / 49.4 / 59.4
+//   520        13.6 / 21.6 / 28.9  26.1 / 34.1 / 42.4  40.2 / 49.5 / 54.8  74.7 / 82.7 / 81.6
+// INT2 and the BF16 cache, and 32 rows (at 64 heads two row blocks: the same
+// lines at 128 and 256 items), fall the same way.
 constexpr int kCus = 256;
 constexpr int narrow_waves(int64_t blocks) { return blocks <= kCus ? 4 : blocks <= 2 * kCus ? 2 : 1; }
 

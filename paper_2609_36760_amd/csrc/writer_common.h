@@ -83,7 +83,7 @@ template <int CTRL>
 __device__ __forceinline__ float dpp(float v) { return __uint_as_float(dpp<CTRL>(__float_as_uint(v))); }
 
 // x / s, correctly rounded, for a bf16 value x and r = RN(1 / s): the product
-// x r corrected once by its exact remainder.  Checked for every mantissa of x
+// x r corrected once by its exact remainder (Markstein's division).  Checked for every mantissa of x
 // and s (2^7 x 2^23 pairs, tests/test_writer_quotient.py); powers of two scale
 // through while s and r are normal and the quotient is far from overflow.  A
 // quotient so small that the remainder underflows (below 2^-40) may be off in
