@@ -36,7 +36,7 @@
  *     num_splits), rounded up to a multiple of 8, times ceil(s_q * H / 128)
  *     exceed 2^24 - 1 (the 16-row kernel, s_q * H <= 32: 2^26 - 1 times
  *     ceil(s_q * H / 16)); a combine of more than 2^24 - 8 rows (B * s_q * H).
- *   - Output bits.  A call repeats itself bit for bit.  The order in which a
+ *   - Output bits.  A decode repeats itself bit for bit.  The order in which a
  *     row's keys are summed follows the launch's shape, which depends on the
  *     cache kind, s_q * H, split_tokens and the number of work items (B
  *     unsplit, else num_splits): the same sequence in a batch of another size,
